@@ -31,6 +31,7 @@
 #include "tile3d.hpp"
 #include "hybrid.hpp"
 #include "fgmres.hpp"
+#include "legs.hpp"
 #include "csr.hpp"
 
 using namespace gkb;
@@ -161,6 +162,7 @@ struct Level {
   // level writes its first sweep from a zero guess in the same pass
   T* dinv = nullptr;
   double omega_e = 0.0;
+  LegPlan leg;  // the level's way down and up as one kernel each (tile 0: not)
 };
 
 template <typename T>
@@ -384,6 +386,15 @@ __global__ __launch_bounds__(kBlock) void k_jacobi_first(int n, T omega, const T
     x[i] = omega * dinv[i] * b[i];
 }
 
+// The level's legs run as one kernel each: the cycles V(2,2) with weighted
+// Jacobi and V(1,1) with the hybrid smoother, on the levels that leg_plan
+// picks (stencil = 1 keeps the separate generic kernels).
+LegPlan level_legs(const gkb_ctx* c, const Grid& g, int elem) {
+  const int nu = c->opt.smoother == GKB_SMOOTH_HYBRID ? 1 : 2;
+  if (c->csr || c->opt.stencil != 0 || c->opt.nu_pre != nu || c->opt.nu_post != nu) return LegPlan();
+  return leg_plan(g, nu == 1, elem);
+}
+
 // first_done: the first pre-smoothing sweep from a zero guess is already in
 // its output buffer (written by the restriction into this level)
 template <typename T>
@@ -401,6 +412,17 @@ void vcycle(gkb_ctx* c, Inner<T>& in, int l, const T* b, T* x, double* dot_parti
   }
   const int n1 = c->opt.nu_pre, n2 = c->opt.nu_post, tot = n1 + n2;
   const T om = T(L.omega);
+  if (L.leg.tile) {
+    Level<T>& Lc = in.lv[l + 1];
+    const LegLevel<T> leg{L.op,    Lc.g, l == 0 ? in.dinv : L.dinv, L.edinv, om,
+                          T(L.omega_e), c->smooth_transfer ? 1 : 0};
+    // a coarse level that runs separate kernels finds its first sweep done
+    T* x0c = (Lc.dinv && !Lc.leg.tile) ? ((tot - 1) % 2 == 0 ? Lc.x : Lc.t) : nullptr;
+    leg_down<T>(s, L.leg, leg, b, L.t, Lc.b, Lc.dinv, T(Lc.omega), x0c, st);
+    vcycle<T>(c, in, l + 1, Lc.b, Lc.x, nullptr, st, x0c != nullptr);
+    leg_up<T>(s, L.leg, leg, Lc.x, L.t, b, x, dot_partial, st);
+    return;
+  }
   const bool hybrid = L.edinv != nullptr;
   // sweep k writes x when (tot - k) is even, else t
   auto dst = [&](int k) { return ((tot - k) % 2 == 0) ? x : L.t; };
@@ -445,7 +467,7 @@ void vcycle(gkb_ctx* c, Inner<T>& in, int l, const T* b, T* x, double* dot_parti
   const dim3 tg = transfer_grid(Lc.g);
   // the coarse level's first sweep (x = omega D^-1 b) goes where its V-cycle
   // puts the first pre-smoothing result
-  T* x0c = (n1 > 0 && Lc.dinv) ? (((tot - 1) % 2 == 0) ? Lc.x : Lc.t) : nullptr;
+  T* x0c = (n1 > 0 && Lc.dinv && !Lc.leg.tile) ? (((tot - 1) % 2 == 0) ? Lc.x : Lc.t) : nullptr;
   const T omc = T(Lc.omega);
   const T* rsrc = cur ? L.rb : b;
   if (cur) face_op<T, kResid>(c, L.op, L.fl, cur, b, L.rb, T(0), nullptr, st);
@@ -514,6 +536,7 @@ template <typename T>
 int vcycle_parts(gkb_ctx* c, Inner<T>& in) {
   if (c->L == 1) return vec_blocks(in.lv[0].g.m_full);
   if (c->opt.nu_post == 0) return vec_blocks(in.lv[0].g.m_full);
+  if (in.lv[0].leg.tile) return in.lv[0].leg.nblocks;
   return in.lv[0].fl.nparts;
 }
 
@@ -1276,6 +1299,7 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
       lv.fl.nparts = lv.fl.gparts = vec_blocks(lv.g.m_full);
     } else {
       lv.fl = face_launch(lv.g, 4, c->opt.stencil);
+      if (l < L - 1) lv.leg = level_legs(c, lv.g, sizeof(T));
     }
     const int m = lv.g.m_full;
     if (l > 0) {
@@ -1433,6 +1457,8 @@ int setup_impl(gkb_ctx* c, const gkb_grid* grid, const double* visc, double eta,
   for (int l = 0; l < L; ++l) {
     maxp = std::max(maxp, face_launch(c->grids[l], 4, c->opt.stencil).nparts);
     maxp = std::max(maxp, face_launch(c->grids[l], 4, 1).nparts);
+    maxp = std::max(maxp, std::max(level_legs(c, c->grids[l], 4).nblocks,
+                                   level_legs(c, c->grids[l], 8).nblocks));
     const dim3 tg = transfer_grid(c->grids[l]);  // learned unpack partials
     maxp = std::max(maxp, (int)(tg.x * tg.z));
     maxp = std::max(maxp, cell_parts(c->grids[l]));

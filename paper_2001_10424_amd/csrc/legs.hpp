@@ -1,0 +1,44 @@
+// Fused V-cycle legs: everything a level does on the way down (pre-smoothing
+// from a zero guess, residual, restriction) in one kernel, and everything on
+// the way up (prolongation, post-smoothing) in another.  Launch interface of
+// legs.hip.
+#pragma once
+#include "common.hpp"
+
+namespace gkb {
+
+// how a level's legs are launched; tile 0: not fused
+struct LegPlan {
+  int tile = 0;
+  dim3 grid;
+  int nblocks = 0;  // partials of the dot product that the way up can form
+};
+
+// plan of a level: size of an element in bytes, hybrid or Jacobi smoother
+LegPlan leg_plan(const Grid& g, bool hybrid, int elem);
+
+// what both legs read of a level
+template <typename T>
+struct LegLevel {
+  Op<T> op;
+  Grid gc;            // next coarser grid
+  const T* dinv;      // 1 / diag(M), 0 at faces that are not unknowns
+  const T* edinv;     // 1 / diag(C^T W C) of the edge sweeps (hybrid)
+  T omega, omega_e;
+  int smooth;         // SMOOTH transfers (else DIV)
+};
+
+// xo = the pre-smoothed iterate from a zero guess (two Jacobi sweeps, or one
+// with an edge sweep), bc = R (b - M xo); x0c (optional): the first sweep
+// from a zero guess on the coarse level, omega_c dinv_c bc
+template <typename T>
+void leg_down(hipStream_t s, const LegPlan& plan, const LegLevel<T>& L, const T* b, T* xo, T* bc,
+              const T* dinv_c, T omega_c, T* x0c, const PcgState* st);
+
+// xo = the post-smoothed iterate from xi + P ec; partial (optional): block
+// partials of b . xo.  xi and xo must not overlap.
+template <typename T>
+void leg_up(hipStream_t s, const LegPlan& plan, const LegLevel<T>& L, const T* ec, const T* xi,
+            const T* b, T* xo, double* partial, const PcgState* st);
+
+}  // namespace gkb

@@ -1,0 +1,72 @@
+"""The fused V-cycle legs (one kernel down, one up per level) against the
+separate generic kernels (stencil = 1) on grids that end inside, at and just
+past their tiles, for every boundary type, both transfers, both smoothers and
+both precisions.
+
+Tolerances: both sides run the same V-cycle in the same precision with sums
+in another order.  A level's operators amplify a rounding by at most
+|M| / |D| <= 3 and a cycle chains fewer than 40 of them, so 1e3 eps of the
+precision bounds the relative difference with room for the levels' sum."""
+import numpy as np
+import pytest
+
+import problems as P
+
+D, N = P.DIRICHLET, P.NATURAL
+
+pytestmark = pytest.mark.gpu
+
+WALLS = (D,) * 6
+GRIDS = {
+    # 8 x 8 tiles: remainders 4 and 2, one cell row past a tile
+    "2d_small": P.Grid(2, (40, 36, 1), 1 / 36, WALLS, 0),
+    "2d_rem2": P.Grid(2, (50, 58, 1), 1 / 58, (D, N, D, D, D, D), -1),
+    "2d_nat": P.Grid(2, (64, 48, 1), 1 / 48, (N, D, D, N, D, D), 64 * 21 + 33),
+    # 32 x 16 tiles: remainder 16, exact
+    "2d_large": P.Grid(2, (368, 368, 1), 1 / 368, WALLS, 367),
+    "2d_large_nat": P.Grid(2, (512, 272, 1), 1 / 272, (D, N, N, D, D, D), -1),
+    # 4^3 tiles, 8 x 8 x 4 tiles, 8^3 tiles
+    "3d_small": P.Grid(3, (10, 12, 14), 1 / 12, WALLS, 5 * 120 + 37),
+    "3d_small_nat": P.Grid(3, (16, 12, 14), 1 / 12, (D, N, N, D, D, N), -1),
+    "3d_medium": P.Grid(3, (20, 20, 18), 1 / 20, WALLS, 0),
+    "3d_medium_nat": P.Grid(3, (36, 20, 24), 1 / 20, (N, D, D, N, N, D), -1),
+    "3d_large": P.Grid(3, (40, 40, 44), 1 / 40, WALLS, 9 * 1600 + 8 * 40 + 7),
+    "3d_large_nat": P.Grid(3, (72, 40, 40), 1 / 40, (D, N, D, D, D, N), -1),
+}
+
+
+def _dev(x, dtype):
+    import torch
+    return torch.tensor(np.asarray(x), dtype=dtype, device="cuda")
+
+
+@pytest.mark.parametrize("smoother,transfer,varmu,precision", [
+    ("jacobi", "div", False, "fp64"), ("jacobi", "smooth", True, "mixed"),
+    ("hybrid", "smooth", False, "mixed"), ("hybrid", "div", True, "fp64")])
+@pytest.mark.parametrize("name", list(GRIDS))
+def test_fused_legs_match_separate_kernels(name, smoother, transfer, varmu, precision):
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] legs", name, smoother, transfer, varmu, precision, flush=True)
+    g = GRIDS[name]
+    mu = np.exp(np.random.default_rng(5).standard_normal(g.n_cells)) if varmu else None
+    nu = 1 if smoother == "hybrid" else 2
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    # entries at faces that are no unknown must not matter
+    r = _dev(np.random.default_rng(11).standard_normal(g.m_full), dt)
+    out = []
+    for stencil in (0, 1):
+        s = gk.Solver(g, mu, 1e2, inner="mg", stencil=stencil, smoother=smoother, nu_pre=nu,
+                      nu_post=nu, mg_transfer=transfer, precision=precision)
+        z = s.precondition(r, precision)
+        out.append(z.double().cpu().numpy())
+        # the level-0 dot partials: PCG needs the same iterations
+        f = _dev(P.random_vector(g, 6), torch.float64)
+        _, it = s.inner_solve(f, 1e-4)
+        out.append(it)
+        s.close()
+    a, ia, b, ib = out
+    eps = 2.0 ** -52 if precision == "fp64" else 2.0 ** -23
+    assert np.linalg.norm(a - b) <= 1e3 * eps * np.linalg.norm(b)
+    assert np.all(a[g.face_mask() == 0] == 0)
+    assert abs(ia - ib) <= 1 + 0.02 * ib, (ia, ib)
