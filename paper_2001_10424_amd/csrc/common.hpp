@@ -57,6 +57,7 @@ struct PcgState {
   double theta;     // energy-optimal weight of the network correction
   double gain;      // error energy removed by that step, (c.rt)^2 / (c.Mc)
   double gain_sum;  // sum over network applications of gain / (r.V(r))
+  double rz_x;      // folded steps: r.z of the current direction, kept for beta
   double ring[10];  // r.r sampled every 5 iterations (stagnation test)
   int it, maxit, done, status, nonfinite;
   int fallback;     // learned preconditioner switched off for this solve
@@ -66,6 +67,108 @@ struct PcgState {
   int fb_it;        // iteration and cause of the fallback (1 descent,
   int fb_reason;    // 2 stagnation, 3 gain below the threshold)
   int gain_n;       // network applications counted in gain_sum
+  int it_x;         // folded steps: iterations before the current one
+  int fresh;        // folded steps: no direction update yet in this solve
 };
+
+// Sum of n partials by every thread of a block of BS threads, in a fixed
+// order, so that all blocks get the same bits: a thread's share (its loads
+// can be in flight with others), then the block's; sh: BS / 64 doubles.
+template <int BS>
+__device__ __forceinline__ double fold_share(const double* __restrict__ part, int n) {
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += BS) v += part[i];
+  return v;
+}
+template <int BS>
+__device__ __forceinline__ double fold_sum(double v, double* sh) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < BS / 64; ++w) s += sh[w];
+  __syncthreads();  // sh may be used again
+  return s;
+}
+
+// Scalar steps of PCG on the device state (one thread): alpha from p.q;
+// the convergence test on r.r (with rz: also beta, Jacobi path); beta from
+// the new r.z.
+__device__ __forceinline__ void pcg_set_alpha(PcgState* st, double pq) {
+  st->pq = pq;
+  const double a = st->rz / pq;
+  if (!(pq > 0.0) || !isfinite(a)) {
+    st->alpha = 0.0;
+    st->nonfinite = 1;
+    st->status = -4;
+    st->done = 1;
+  } else {
+    st->alpha = a;
+  }
+}
+__device__ __forceinline__ void pcg_set_check(PcgState* st, double rr, bool has_rz, double rz) {
+  st->rr = rr;
+  st->it += 1;
+  // r.r sampled every 5 iterations: stagnant when no decrease over 50
+  // (CG minimises the energy norm, so r.r may rise over shorter spans)
+  if (st->it % 5 == 0) {
+    const int slot = (st->it / 5) % 10;
+    if (st->it > 50 && rr >= st->ring[slot]) st->stagnant = 1;
+    st->ring[slot] = rr;
+  }
+  if (!isfinite(rr)) {
+    st->nonfinite = 1;
+    st->status = -4;
+    st->done = 1;
+  } else if (rr <= st->tol2 * st->rr0) {
+    st->done = 1;
+    st->status = 0;
+  } else if (st->it >= st->maxit) {
+    st->done = 1;
+    st->status = -5;
+  } else if (has_rz) {
+    st->beta = rz / st->rz;
+    st->rz = rz;
+  }
+}
+__device__ __forceinline__ void pcg_set_beta(PcgState* st, double rz) {
+  st->beta = rz / st->rz;
+  st->rz = rz;
+}
+
+// Folded scalar steps.  Where a PCG iteration is bound by its launches, the
+// scalar steps are not kernels of their own: every block of the kernel that
+// needs the scalar sums the (few) partials itself, in the same order, and
+// block 0 records it.  No kernel reads a field that it writes itself: the
+// product (A) reads rz_x and fresh and writes rz and beta; the update (X)
+// reads rz and it and writes alpha, rz_x, it_x and fresh; the first V-cycle
+// kernel (C) reads it_x and writes it and the outcome.  done is written by X
+// and C only when every block of them comes to the same end by itself.
+__device__ __forceinline__ double fold_beta(PcgState* st, double rz_new, bool lead) {
+  if (st->fresh) return 0.0;  // p = z: rz is that of the start
+  const double b = rz_new / st->rz_x;
+  if (lead) {
+    st->rz = rz_new;
+    st->beta = b;
+  }
+  return b;
+}
+__device__ __forceinline__ double fold_alpha(PcgState* st, double pq, bool lead) {
+  const double rz = st->rz, a = rz / pq;
+  if (lead) {
+    pcg_set_alpha(st, pq);
+    st->rz_x = rz;
+    st->it_x = st->it;
+    st->fresh = 0;
+  }
+  return (!(pq > 0.0) || !isfinite(a)) ? 0.0 : a;
+}
+// true: the iteration ends here
+__device__ __forceinline__ bool fold_check(PcgState* st, double rr, bool lead) {
+  const bool end = !isfinite(rr) || rr <= st->tol2 * st->rr0 || st->it_x + 1 >= st->maxit;
+  if (lead) pcg_set_check(st, rr, false, 0.0);
+  return end;
+}
 
 }  // namespace gkb

@@ -59,6 +59,10 @@ constexpr int kSlots = 6;
 constexpr int kMaxRestart = kGmMaxRestart;  // inner FGMRES Krylov vectors
 constexpr int kMaxOuterRestart = 32;  // outer FGMRES (GKB as preconditioner)
 
+// blocks of the folded PCG update: an entry per thread, at most 1024 (their
+// partials are summed by every block of the next kernel)
+constexpr int kFoldParts = 2048;  // most partials that the scalar steps fold
+int fold_blocks(int n) { return std::max(1, std::min((n + kBlock - 1) / kBlock, 1024)); }
 int vec_blocks(int n) { return std::max(1, std::min((n + 1023) / 1024, 4096)); }
 
 struct FaceLaunch {
@@ -396,10 +400,11 @@ LegPlan level_legs(const gkb_ctx* c, const Grid& g, int elem) {
 }
 
 // first_done: the first pre-smoothing sweep from a zero guess is already in
-// its output buffer (written by the restriction into this level)
+// its output buffer (written by the restriction into this level); check: the
+// convergence test that the level's way down takes along (fused legs only)
 template <typename T>
 void vcycle(gkb_ctx* c, Inner<T>& in, int l, const T* b, T* x, double* dot_partial,
-            const PcgState* st, bool first_done = false) {
+            const PcgState* st, bool first_done = false, const FoldCheck& check = FoldCheck()) {
   Level<T>& L = in.lv[l];
   hipStream_t s = c->cs;
   if (l == c->L - 1) {
@@ -418,7 +423,7 @@ void vcycle(gkb_ctx* c, Inner<T>& in, int l, const T* b, T* x, double* dot_parti
                           T(L.omega_e), c->smooth_transfer ? 1 : 0};
     // a coarse level that runs separate kernels finds its first sweep done
     T* x0c = (Lc.dinv && !Lc.leg.tile) ? ((tot - 1) % 2 == 0 ? Lc.x : Lc.t) : nullptr;
-    leg_down<T>(s, L.leg, leg, b, L.t, Lc.b, Lc.dinv, T(Lc.omega), x0c, st);
+    leg_down<T>(s, L.leg, leg, b, L.t, Lc.b, Lc.dinv, T(Lc.omega), x0c, st, check);
     vcycle<T>(c, in, l + 1, Lc.b, Lc.x, nullptr, st, x0c != nullptr);
     leg_up<T>(s, L.leg, leg, Lc.x, L.t, b, x, dot_partial, st);
     return;
@@ -569,6 +574,26 @@ int pcg_iterations(gkb_ctx* c, Inner<T>& in, int count) {
   // kernel needs 152 VGPRs, one wave per SIMD fewer than the plain product,
   // and measured 2 % slower per iteration
   const bool fused = sizeof(T) == 4 && !jac && L0.fl.tiled && in.p2 && count % 2 == 0;
+  // Where the finest level runs fused legs, an iteration is bound by its
+  // launches: the direction update joins the product (alternating as above)
+  // and the three scalar steps join the kernels that need them, 4 + legs
+  // kernels instead of 7 + legs (common.hpp).
+  const LegPlan ap = L0.leg.tile ? apply_plan(L0.g) : LegPlan();
+  if (!jac && ap.tile && std::max(ap.nblocks, L0.leg.nblocks) <= kFoldParts && in.p2) {
+    const int xb = fold_blocks(n);
+    for (int it = 0; it < count; ++it) {
+      T* pold = (it % 2 == 0) ? in.p : in.p2;
+      T* pd = (it % 2 == 0) ? in.p2 : in.p;
+      leg_apply<T>(s, ap, L0.op, in.z, pold, in.q, pd, c->part[0], in.st, c->part[2],
+                   L0.leg.nblocks);
+      k_pcg_xr_fold<T><<<xb, kBlock, 0, s>>>(n, in.st, c->part[0], ap.nblocks, pd, in.q, in.x,
+                                             in.r, c->part[1]);
+      vcycle<T>(c, in, 0, in.r, in.z, c->part[2], in.st, false, FoldCheck{in.st, c->part[1], xb});
+    }
+    // an odd count ends in in.p2: the next one starts from in.p
+    if (count % 2 != 0) k_cast<T, T><<<vb, kBlock, 0, s>>>(n, in.p2, in.p);
+    return GKB_OK;
+  }
   for (int it = 0; it < count; ++it) {
     T* pd = in.p;  // direction of this iteration
     if (fused) {
@@ -1327,7 +1352,8 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
   CK(c->mem.arr(&in.r, m));
   CK(c->mem.arr(&in.z, m));
   CK(c->mem.arr(&in.p, m));
-  if (sizeof(T) == 4 && c->fl0.tiled && c->opt.inner != GKB_INNER_JACOBI) CK(c->mem.arr(&in.p2, m));
+  if (((sizeof(T) == 4 && c->fl0.tiled) || in.lv[0].leg.tile) && c->opt.inner != GKB_INNER_JACOBI)
+    CK(c->mem.arr(&in.p2, m));
   CK(c->mem.arr(&in.q, m));
   CK(c->mem.arr(&in.rprev, m));
   CK(c->mem.arr(&in.st, 1));
@@ -1463,6 +1489,8 @@ int setup_impl(gkb_ctx* c, const gkb_grid* grid, const double* visc, double eta,
     maxp = std::max(maxp, (int)(tg.x * tg.z));
     maxp = std::max(maxp, cell_parts(c->grids[l]));
     maxp = std::max(maxp, vec_blocks(c->grids[l].m_full));
+    maxp = std::max(maxp, fold_blocks(c->grids[l].m_full));
+    maxp = std::max(maxp, apply_plan(c->grids[l]).nblocks);
   }
   c->maxparts = maxp;
   for (int i = 0; i < kSlots; ++i) CK(c->mem.arr(&c->part[i], maxp));

@@ -337,6 +337,9 @@ __global__ __launch_bounds__(kFinal) void k_pcg_start(PcgState* st, const double
     st->maxit = maxit;
     st->alpha = st->beta = st->pq = 0.0;
     st->rz_prev = rz;
+    st->rz_x = rz;
+    st->it_x = 0;
+    st->fresh = 1;
     st->nonfinite = 0;
     st->done = (ff == 0.0) ? 1 : 0;
     st->status = 0;
@@ -346,51 +349,6 @@ __global__ __launch_bounds__(kFinal) void k_pcg_start(PcgState* st, const double
     st->gain_n = 0;
     for (int i = 0; i < 10; ++i) st->ring[i] = 0.0;
   }
-}
-
-// Scalar steps of PCG on the device state (one thread): alpha from p.q;
-// the convergence test on r.r (with rz: also beta, Jacobi path); beta from
-// the new r.z.
-__device__ __forceinline__ void pcg_set_alpha(PcgState* st, double pq) {
-  st->pq = pq;
-  const double a = st->rz / pq;
-  if (!(pq > 0.0) || !isfinite(a)) {
-    st->alpha = 0.0;
-    st->nonfinite = 1;
-    st->status = -4;
-    st->done = 1;
-  } else {
-    st->alpha = a;
-  }
-}
-__device__ __forceinline__ void pcg_set_check(PcgState* st, double rr, bool has_rz, double rz) {
-  st->rr = rr;
-  st->it += 1;
-  // r.r sampled every 5 iterations: stagnant when no decrease over 50
-  // (CG minimises the energy norm, so r.r may rise over shorter spans)
-  if (st->it % 5 == 0) {
-    const int slot = (st->it / 5) % 10;
-    if (st->it > 50 && rr >= st->ring[slot]) st->stagnant = 1;
-    st->ring[slot] = rr;
-  }
-  if (!isfinite(rr)) {
-    st->nonfinite = 1;
-    st->status = -4;
-    st->done = 1;
-  } else if (rr <= st->tol2 * st->rr0) {
-    st->done = 1;
-    st->status = 0;
-  } else if (st->it >= st->maxit) {
-    st->done = 1;
-    st->status = -5;
-  } else if (has_rz) {
-    st->beta = rz / st->rz;
-    st->rz = rz;
-  }
-}
-__device__ __forceinline__ void pcg_set_beta(PcgState* st, double rz) {
-  st->beta = rz / st->rz;
-  st->rz = rz;
 }
 
 // The one-block scalar kernels below read the done flag together with the
@@ -440,6 +398,39 @@ __global__ __launch_bounds__(kBlock) void k_pcg_xr(int n, const PcgState* __rest
     v = block_sum<kBlock>(t, sh);
     if (threadIdx.x == 0) part_rz[blockIdx.x] = v;
   }
+}
+
+// The same update with alpha folded in: every block sums the npq partials of
+// p.q (folded scalar steps, common.hpp).  Its blocks are small (one entry per
+// thread up to 2^18 entries), so the loads, the partials among them, are one
+// round trip.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_pcg_xr_fold(int n, PcgState* st,
+                                                        const double* __restrict__ part_pq, int npq,
+                                                        const T* __restrict__ p,
+                                                        const T* __restrict__ q,
+                                                        T* __restrict__ x, T* __restrict__ r,
+                                                        double* __restrict__ part_rr) {
+  __shared__ double sh[kBlock / 64];
+  const int done = st->done;
+  int i = blockIdx.x * kBlock + threadIdx.x;
+  const int e = i < n ? i : 0;
+  T xi = x[e], pi = p[e], ri = r[e], qi = q[e];
+  const double share = fold_share<kBlock>(part_pq, npq);
+  if (done) return;
+  const double pq = fold_sum<kBlock>(share, sh);
+  const T a = T(fold_alpha(st, pq, blockIdx.x == 0 && threadIdx.x == 0));
+  double s = 0.0;
+  while (i < n) {
+    x[i] = xi + a * pi;
+    ri = ri - a * qi;
+    r[i] = ri;
+    s += double(ri) * double(ri);
+    i += gridDim.x * kBlock;
+    if (i < n) xi = x[i], pi = p[i], ri = r[i], qi = q[i];
+  }
+  const double v = block_sum<kBlock>(s, sh);
+  if (threadIdx.x == 0) part_rr[blockIdx.x] = v;
 }
 
 // convergence test on r.r; with part_rz also the CG beta (Jacobi path)

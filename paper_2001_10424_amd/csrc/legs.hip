@@ -22,12 +22,12 @@ struct Tile {
   static constexpr int DIM = DIM_, TX = X, TY = Y, TZ = Z, NT = NT_;
 };
 
-// LDS box of a tile with halo H
-template <class TL, int H_>
+// LDS box of a tile with halo H below and HU above
+template <class TL, int H_, int HU = H_>
 struct Box {
   static constexpr int H = H_, DIM = TL::DIM;
-  static constexpr int EX = TL::TX + 2 * H, EY = TL::TY + 2 * H,
-                       EZ = DIM == 3 ? TL::TZ + 2 * H : 1;
+  static constexpr int EX = TL::TX + H + HU, EY = TL::TY + H + HU,
+                       EZ = DIM == 3 ? TL::TZ + H + HU : 1;
   static constexpr int N = EX * EY * EZ;
   static constexpr int SY = EX, SZ = EX * EY;
 };
@@ -468,8 +468,8 @@ template <typename T, class TL, bool VARMU, bool HYB>
 __global__ __launch_bounds__(TL::NT) void k_leg_down(LegLevel<T> L, const T* __restrict__ b,
                                                      T* __restrict__ xo, T* __restrict__ bc,
                                                      const T* __restrict__ dinv_c, T omega_c,
-                                                     T* __restrict__ x0c,
-                                                     const PcgState* __restrict__ st) {
+                                                     T* __restrict__ x0c, const PcgState* st,
+                                                     FoldCheck check) {
   typedef Box<TL, HYB ? 4 : 3> B;
   constexpr int DIM = B::DIM, N = B::N, H = B::H;
   __shared__ T X[DIM * N];
@@ -492,7 +492,14 @@ __global__ __launch_bounds__(TL::NT) void k_leg_down(LegLevel<T> L, const T* __r
   a1.load(G, HYB ? b : L.dinv, i0, j0, k0);
   if constexpr (HYB) ed.load(L, i0, j0, k0);
   br.load(G, b, i0, j0, k0);
+  const double share = check.part ? fold_share<TL::NT>(check.part, check.n) : 0.0;
   if (done) return;
+  if (check.part) {  // uniform
+    __shared__ double sh[TL::NT / 64];
+    const double rr = fold_sum<TL::NT>(share, sh);
+    const bool lead = threadIdx.x == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0;
+    if (fold_check(check.st, rr, lead)) return;
+  }
   const bool special = fill_edges<T, TL, B>(G, E, i0, j0, k0);
   // first sweep from a zero guess
 #pragma unroll
@@ -711,12 +718,78 @@ __global__ __launch_bounds__(TL::NT) void k_leg_up(LegLevel<T> L, const T* __res
   }
 }
 
+// The product of a PCG iteration with the direction update, beta folded in
+// (halo 1, and one layer more above: the boundary faces behind the tile).
+template <typename T, class TL, bool VARMU>
+__global__ __launch_bounds__(TL::NT) void k_leg_apply(Op<T> op, const T* __restrict__ z,
+                                                      const T* __restrict__ p, T* __restrict__ q,
+                                                      T* __restrict__ pn,
+                                                      double* __restrict__ part_pq, PcgState* st,
+                                                      const double* __restrict__ part_rz, int nrz) {
+  typedef Box<TL, 1, 2> B;
+  constexpr int DIM = B::DIM, N = B::N, H = 1;
+  __shared__ T X[DIM * N];
+  __shared__ Edges<T, B> E;
+  __shared__ double sh[TL::NT / 64];
+  const int done = st->done;
+  const Grid& G = op.g;
+  const int ti = blockIdx.x * TL::TX, tj = blockIdx.y * TL::TY, tk = blockIdx.z * TL::TZ;
+  const int i0 = ti - H, j0 = tj - H, k0 = DIM == 3 ? tk - H : 0;
+  typedef Sites<TL, B, 0, 0> SA;
+  Ahead<T, SA, DIM> za, pa;
+  za.load(G, z, i0, j0, k0);
+  pa.load(G, p, i0, j0, k0, za.on);
+  const double share = fold_share<TL::NT>(part_rz, nrz);
+  if (done) return;
+  const bool special = fill_edges<T, TL, B>(G, E, i0, j0, k0);
+  const double rz = fold_sum<TL::NT>(share, sh);
+  const bool lead = threadIdx.x == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0;
+  const T beta = T(fold_beta(st, rz, lead));
+#pragma unroll
+  for (int e = 0; e < SA::PER; ++e) {
+    SA t;
+    if (!t.get(e)) continue;
+#pragma unroll
+    for (int c = 0; c < DIM; ++c)
+      X[c * N + t.s] = za.unk(e, c) ? za.v[e][c] + beta * pa.v[e][c] : T(0);
+  }
+  __syncthreads();
+  double part = 0.0;
+  typedef Sites<TL, B, 1, 1> SO;  // own sites and the boundary faces behind them
+#pragma unroll
+  for (int e = 0; e < SO::PER; ++e) {
+    SO t;
+    if (!t.get(e)) continue;
+    const int i = i0 + t.x, j = j0 + t.y, k = k0 + t.z;
+    T m[3];
+    row_M<T, VARMU, B>(op, E, special, X, t, i, j, k, m);
+    const unsigned on = unknown_bits<DIM>(G, i, j, k);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+      if (!owned<TL>(G, c, t.x - H, t.y - H, DIM == 3 ? t.z - H : 0, i, j, k)) continue;
+      T v = T(0), w = T(0);
+      if ((on >> c) & 1u) {
+        w = X[c * N + t.s];
+        v = m[c];
+        part += double(w) * double(v);
+      }
+      const int f = face(G, c, i, j, k);
+      q[f] = v;
+      pn[f] = w;
+    }
+  }
+  const double s = block_sum<TL::NT>(part, sh);
+  if (threadIdx.x == 0)
+    part_pq[blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)] = s;
+}
+
 // tiles: 2D small and large, 3D small, medium and large
 typedef Tile<2, 8, 8, 1, 256> T2S;
 typedef Tile<2, 32, 16, 1, 512> T2L;
 typedef Tile<3, 4, 4, 4, 512> T3S;
 typedef Tile<3, 8, 8, 4, 512> T3M;
 typedef Tile<3, 8, 8, 8, 512> T3L;
+typedef Tile<2, 16, 8, 1, 256> T2P;  // product only (halo 1): small 2D levels
 
 template <class TL>
 LegPlan plan_of(const Grid& g, int id) {
@@ -730,11 +803,11 @@ LegPlan plan_of(const Grid& g, int id) {
 
 template <typename T, class TL, bool HYB>
 void launch_down(hipStream_t s, const LegPlan& p, const LegLevel<T>& L, const T* b, T* xo, T* bc,
-                 const T* dinv_c, T omega_c, T* x0c, const PcgState* st) {
+                 const T* dinv_c, T omega_c, T* x0c, const PcgState* st, const FoldCheck& ck) {
   if (L.op.mu)
-    k_leg_down<T, TL, true, HYB><<<p.grid, TL::NT, 0, s>>>(L, b, xo, bc, dinv_c, omega_c, x0c, st);
+    k_leg_down<T, TL, true, HYB><<<p.grid, TL::NT, 0, s>>>(L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
   else
-    k_leg_down<T, TL, false, HYB><<<p.grid, TL::NT, 0, s>>>(L, b, xo, bc, dinv_c, omega_c, x0c, st);
+    k_leg_down<T, TL, false, HYB><<<p.grid, TL::NT, 0, s>>>(L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
 }
 
 template <typename T, class TL, bool HYB>
@@ -771,30 +844,56 @@ LegPlan leg_plan(const Grid& g, bool hybrid, int elem) {
   return p.nblocks <= 256 ? p : LegPlan();
 }
 
+LegPlan apply_plan(const Grid& g) {
+  if (g.dim == 2) return g.n_cells >= (1 << 17) ? plan_of<T2L>(g, 2) : plan_of<T2P>(g, 1);
+  return g.n_cells <= 32 * 32 * 32 ? plan_of<T3M>(g, 4) : plan_of<T3L>(g, 5);
+}
+
+template <typename T, class TL>
+void launch_apply(hipStream_t s, const LegPlan& p, const Op<T>& op, const T* z, const T* pv, T* q,
+                  T* pn, double* part_pq, PcgState* st, const double* part_rz, int nrz) {
+  if (op.mu)
+    k_leg_apply<T, TL, true><<<p.grid, TL::NT, 0, s>>>(op, z, pv, q, pn, part_pq, st, part_rz, nrz);
+  else
+    k_leg_apply<T, TL, false><<<p.grid, TL::NT, 0, s>>>(op, z, pv, q, pn, part_pq, st, part_rz, nrz);
+}
+
+template <typename T>
+void leg_apply(hipStream_t s, const LegPlan& p, const Op<T>& op, const T* z, const T* pv, T* q,
+               T* pn, double* part_pq, PcgState* st, const double* part_rz, int nrz) {
+  switch (p.tile) {
+    case 1: launch_apply<T, T2P>(s, p, op, z, pv, q, pn, part_pq, st, part_rz, nrz); break;
+    case 2: launch_apply<T, T2L>(s, p, op, z, pv, q, pn, part_pq, st, part_rz, nrz); break;
+    case 4: launch_apply<T, T3M>(s, p, op, z, pv, q, pn, part_pq, st, part_rz, nrz); break;
+    case 5: launch_apply<T, T3L>(s, p, op, z, pv, q, pn, part_pq, st, part_rz, nrz); break;
+  }
+}
+
 template <typename T>
 void leg_down(hipStream_t s, const LegPlan& p, const LegLevel<T>& L, const T* b, T* xo, T* bc,
-              const T* dinv_c, T omega_c, T* x0c, const PcgState* st) {
+              const T* dinv_c, T omega_c, T* x0c, const PcgState* st,
+              const FoldCheck& ck) {
   const bool hyb = L.edinv != nullptr;
   switch (p.tile) {
     case 1:
-      if (hyb) launch_down<T, T2S, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
-      else launch_down<T, T2S, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
+      if (hyb) launch_down<T, T2S, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
+      else launch_down<T, T2S, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
       break;
     case 2:
-      if (hyb) launch_down<T, T2L, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
-      else launch_down<T, T2L, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
+      if (hyb) launch_down<T, T2L, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
+      else launch_down<T, T2L, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
       break;
     case 3:
-      if (hyb) launch_down<T, T3S, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
-      else launch_down<T, T3S, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
+      if (hyb) launch_down<T, T3S, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
+      else launch_down<T, T3S, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
       break;
     case 4:
-      if (!hyb) launch_down<T, T3M, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
+      if (!hyb) launch_down<T, T3M, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
       else if constexpr (sizeof(T) == 4)  // FP64 needs more LDS than a CU has
-        launch_down<T, T3M, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
+        launch_down<T, T3M, true>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
       break;
     case 5:
-      launch_down<T, T3L, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st);
+      launch_down<T, T3L, false>(s, p, L, b, xo, bc, dinv_c, omega_c, x0c, st, ck);
       break;
   }
 }
@@ -827,10 +926,18 @@ void leg_up(hipStream_t s, const LegPlan& p, const LegLevel<T>& L, const T* ec, 
   }
 }
 
+template void leg_apply<float>(hipStream_t, const LegPlan&, const Op<float>&, const float*,
+                               const float*, float*, float*, double*, PcgState*, const double*,
+                               int);
+template void leg_apply<double>(hipStream_t, const LegPlan&, const Op<double>&, const double*,
+                                const double*, double*, double*, double*, PcgState*,
+                                const double*, int);
 template void leg_down<float>(hipStream_t, const LegPlan&, const LegLevel<float>&, const float*,
-                              float*, float*, const float*, float, float*, const PcgState*);
+                              float*, float*, const float*, float, float*, const PcgState*,
+                              const FoldCheck&);
 template void leg_down<double>(hipStream_t, const LegPlan&, const LegLevel<double>&, const double*,
-                               double*, double*, const double*, double, double*, const PcgState*);
+                               double*, double*, const double*, double, double*, const PcgState*,
+                               const FoldCheck&);
 template void leg_up<float>(hipStream_t, const LegPlan&, const LegLevel<float>&, const float*,
                             const float*, const float*, float*, double*, const PcgState*);
 template void leg_up<double>(hipStream_t, const LegPlan&, const LegLevel<double>&, const double*,

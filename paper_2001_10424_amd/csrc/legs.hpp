@@ -28,12 +28,28 @@ struct LegLevel {
   int smooth;         // SMOOTH transfers (else DIV)
 };
 
+// the product of a PCG iteration whose scalar steps are folded (common.hpp):
+// p' = z + beta p with beta from the nrz partials of r.z, q = M p', partials
+// of p'.q; p and pn must not overlap
+LegPlan apply_plan(const Grid& g);
+template <typename T>
+void leg_apply(hipStream_t s, const LegPlan& plan, const Op<T>& op, const T* z, const T* p, T* q,
+               T* pn, double* part_pq, PcgState* st, const double* part_rz, int nrz);
+
+// partials of r.r whose convergence test is folded into the way down
+struct FoldCheck {
+  PcgState* st = nullptr;
+  const double* part = nullptr;
+  int n = 0;
+};
+
 // xo = the pre-smoothed iterate from a zero guess (two Jacobi sweeps, or one
 // with an edge sweep), bc = R (b - M xo); x0c (optional): the first sweep
 // from a zero guess on the coarse level, omega_c dinv_c bc
 template <typename T>
 void leg_down(hipStream_t s, const LegPlan& plan, const LegLevel<T>& L, const T* b, T* xo, T* bc,
-              const T* dinv_c, T omega_c, T* x0c, const PcgState* st);
+              const T* dinv_c, T omega_c, T* x0c, const PcgState* st,
+              const FoldCheck& check = FoldCheck());
 
 // xo = the post-smoothed iterate from xi + P ec; partial (optional): block
 // partials of b . xo.  xi and xo must not overlap.

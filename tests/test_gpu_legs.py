@@ -60,9 +60,13 @@ def test_fused_legs_match_separate_kernels(name, smoother, transfer, varmu, prec
                       nu_post=nu, mg_transfer=transfer, precision=precision)
         z = s.precondition(r, precision)
         out.append(z.double().cpu().numpy())
-        # the level-0 dot partials: PCG needs the same iterations
+        # PCG with its scalar steps folded into the product, the update and
+        # the way down (stencil = 0) needs the same iterations, and its
+        # recursive residual is the true one (FP32 iterates: to their rounding)
         f = _dev(P.random_vector(g, 6), torch.float64)
-        _, it = s.inner_solve(f, 1e-4)
+        x, it = s.inner_solve(f, 1e-4)
+        res = f - s.apply("M", x)
+        assert float(res.norm() / f.norm()) <= (1.0001e-4 if precision == "fp64" else 1e-2)
         out.append(it)
         s.close()
     a, ia, b, ib = out
@@ -70,3 +74,26 @@ def test_fused_legs_match_separate_kernels(name, smoother, transfer, varmu, prec
     assert np.linalg.norm(a - b) <= 1e3 * eps * np.linalg.norm(b)
     assert np.all(a[g.face_mask() == 0] == 0)
     assert abs(ia - ib) <= 1 + 0.02 * ib, (ia, ib)
+
+
+@pytest.mark.parametrize("n", [32, 56])
+def test_direction_buffers_alternate_for_any_chunk(n):
+    """FP32 PCG alternates between two direction buffers: chunks of an even
+    and of an odd number of iterations, and single iterations, are the same
+    arithmetic (32^3: folded steps; 56^3: the separate kernels, where an odd
+    chunk runs the plain update, whose result is the same bits up to the
+    contraction of one multiply-add)."""
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] chunks", n, flush=True)
+    pr = P.stokes_problem(3, n, seed=6, eta=10.0)
+    f = _dev(pr.g, torch.float64)
+    out = []
+    for chunk in (8, 5, 1):
+        s = gk.Solver(pr.grid, None, pr.eta, inner="mg", precision="mixed", check_every=chunk)
+        x, it = s.inner_solve(f, 1e-4)
+        out.append((x, it))
+        s.close()
+    for x, it in out[1:]:
+        assert it == out[0][1]
+        assert float((x - out[0][0]).norm() / x.norm()) <= (0.0 if n == 32 else 1e-5)
