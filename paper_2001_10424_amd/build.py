@@ -21,7 +21,7 @@ FLAGS = [
 ]
 
 
-SOURCES = ("gkb.hip", "legs.hip")
+SOURCES = ("gkb.hip", "legs.hip", "conv.hip")
 
 
 def sources():

@@ -1,17 +1,11 @@
-// Convolutional preconditioner network on gfx950 (see include/gkb_cnn.h).
+// Convolutional preconditioner network on gfx950 (see include/gkb_cnn.h):
+// layers, loss, Adam and checkpoints; the convolution and weight-gradient
+// kernels are in conv.hip.
 //
-// Convolutions are implicit GEMMs on v_mfma_f32_16x16x16_bf16: a wave64
-// computes 16 output points x 16 output channels; the GEMM K dimension runs
-// over taps x input channels, 16 deep per MFMA: one tap of 16 channels, two
-// taps of 8 or four taps of 4 (a layer reads only the channel group its
-// input fills, so 8- and 4-channel inputs take 2x and 4x fewer MFMAs and
-// gathered bytes).
-// Activations are channels-last BF16 padded to 16 channels (32 bytes per
-// point), so the A fragment of a lane (4 consecutive channels of one point)
-// is one 8-byte load; the 3x3(x3) weights of a layer sit in LDS in the
-// B-fragment order [tap][c_out][c_in].  The weight gradient is a GEMM over
-// points (K = points) with one accumulator tile per tap; blocks write FP32
-// partials that a second kernel sums in a fixed order (deterministic).
+// Activations are channels-last BF16, stored with 4, 8 or 16 channels per
+// point (the smallest that holds the layer's); the network's FP32 input and
+// the FP32 output gradient are rounded to BF16 as they are read.  All
+// reductions are deterministic.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -22,269 +16,11 @@
 #include <vector>
 
 #include "../../include/gkb_cnn.h"
+#include "conv.hpp"
 
 namespace gkb {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kCP = 16;        // padded channel count
 constexpr int kMaxLayers = 8;
-
-__host__ __device__ inline uint16_t f2bf(float f) {
-  uint32_t u;
-  std::memcpy(&u, &f, 4);
-  u += 0x7FFFu + ((u >> 16) & 1u);  // round to nearest even
-  return uint16_t(u >> 16);
-}
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
-
-struct CnnGeom {
-  int nx, ny, nz, batch;
-  long P;  // nx * ny * nz * batch
-};
-
-__device__ __forceinline__ void tap_off(int t, int dim, int& dx, int& dy, int& dz) {
-  dx = t % 3 - 1;
-  dy = (t / 3) % 3 - 1;
-  dz = dim == 3 ? t / 9 - 1 : 0;
-}
-
-// neighbour of point p (coordinates i, j, k in one grid) at offset; -1 if
-// outside the grid
-__device__ __forceinline__ long nb_index(const CnnGeom& g, long p, int i, int j, int k, int dx,
-                                         int dy, int dz) {
-  const int ii = i + dx, jj = j + dy, kk = k + dz;
-  if (ii < 0 || ii >= g.nx || jj < 0 || jj >= g.ny || kk < 0 || kk >= g.nz) return -1;
-  return p + dx + (long)dy * g.nx + (long)dz * g.nx * g.ny;
-}
-
-// coordinates of point p in its grid, in 32-bit arithmetic (every network
-// call keeps batch * points below 2^31)
-__device__ __forceinline__ void coords(const CnnGeom& g, long p, int& i, int& j, int& k) {
-  const unsigned q = unsigned(p), nx = unsigned(g.nx), ny = unsigned(g.ny);
-  const unsigned r = q / nx, s = r / ny;
-  i = int(q - r * nx);
-  j = int(r - s * ny);
-  k = int(s % unsigned(g.nz));
-}
-
-enum ConvOut { kOutReluBf16 = 0, kOutF32 = 1, kOutMaskBf16 = 2 };
-
-// Blocks for a convolution over P points: each block stages the layer's
-// weights in LDS once and then takes groups of 64 points (16 per wave) in a
-// grid-stride loop, so the weight staging is paid per block, not per group.
-// At most 8192 blocks: a 64^3 x 2 training batch keeps one group per block
-// (a 2048-block cap, four groups per block, made its gradient layers 25 %
-// slower: each wave waits on its loads group after group), and a 128^3
-// inference pass takes four groups per block.
-inline int conv_blocks(long P) {
-  const long groups = (P + 63) / 64;
-  return int(groups < 8192 ? groups : 8192);
-}
-
-// out[p][n] = bias[n] + sum_tap sum_c in[p + off(tap)][c] * w[tap][n][c],
-// the input channels c < CG (16, 8 or 4; the padded channels above are zero)
-template <int DIM, int OUT, int CG = kCP>
-__global__ __launch_bounds__(256) void k_conv(CnnGeom g, const uint16_t* __restrict__ in,
-                                              const uint16_t* __restrict__ w,
-                                              const float* __restrict__ bias, void* __restrict__ out,
-                                              const uint16_t* __restrict__ mask,
-                                              const int* __restrict__ skip1 = nullptr,
-                                              const int* __restrict__ skip2 = nullptr) {
-  constexpr int TAPS = DIM == 2 ? 9 : 27;
-  static_assert(CG == 16 || CG == 8 || CG == 4, "channel group");
-  constexpr int TPM = kCP / CG;  // taps per MFMA
-  // device-side switches (solve converged / learned correction disabled)
-  if ((skip1 && *skip1) || (skip2 && *skip2)) return;
-  __shared__ uint16_t sw[TAPS * 256];
-  for (int e = threadIdx.x; e < TAPS * 256; e += 256) sw[e] = w[e];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int m = lane & 15, kg = lane >> 4;
-  // the lane's four K values: tap t + tsub, channels c0 .. c0 + 3
-  const int tsub = CG == 16 ? 0 : (CG == 8 ? kg >> 1 : kg);
-  const int c0 = CG == 16 ? 4 * kg : (CG == 8 ? 4 * (kg & 1) : 0);
-  for (long base = (long)blockIdx.x * 64; base < g.P; base += (long)gridDim.x * 64) {
-    const long p0 = base + wv * 16;
-    if (p0 >= g.P) break;
-    const long p = p0 + m;
-    const bool valid = p < g.P;
-    int i = 0, j = 0, k = 0;
-    if (valid) coords(g, p, i, j, k);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t0 = 0; t0 < TAPS; t0 += TPM) {
-      const int t = t0 + tsub;
-      int dx, dy, dz;
-      tap_off(t, DIM, dx, dy, dz);
-      bf16x4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
-      if (t < TAPS) {  // the last group of a layer may run past the taps
-        if (valid) {
-          const long q = nb_index(g, p, i, j, k, dx, dy, dz);
-          if (q >= 0) a = *reinterpret_cast<const bf16x4*>(in + q * kCP + c0);
-        }
-        b = *reinterpret_cast<const bf16x4*>(sw + t * 256 + m * 16 + c0);
-      }
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-    }
-    // acc[q] = D[row 4kg+q][col m]: point p0 + 4kg + q, channel m
-    const float bm = bias ? bias[m] : 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const long pq = p0 + 4 * kg + q;
-      if (pq >= g.P) continue;
-      float v = acc[q] + bm;
-      if (OUT == kOutReluBf16) {
-        static_cast<uint16_t*>(out)[pq * kCP + m] = f2bf(v > 0.f ? v : 0.f);
-      } else if (OUT == kOutF32) {
-        static_cast<float*>(out)[pq * kCP + m] = v;
-      } else {
-        const uint16_t h = mask[pq * kCP + m];
-        const bool pos = h != 0 && (h & 0x8000u) == 0;
-        static_cast<uint16_t*>(out)[pq * kCP + m] = f2bf(pos ? v : 0.f);
-      }
-    }
-  }
-}
-
-// Launch k_conv with the smallest channel group that holds the input's
-// cin channels.
-template <int DIM, int OUT>
-void launch_conv(int cin, int blocks, hipStream_t s, const CnnGeom& g, const uint16_t* in,
-                 const uint16_t* w, const float* bias, void* out, const uint16_t* mask,
-                 const int* skip1 = nullptr, const int* skip2 = nullptr) {
-  if (cin <= 4)
-    k_conv<DIM, OUT, 4><<<blocks, 256, 0, s>>>(g, in, w, bias, out, mask, skip1, skip2);
-  else if (cin <= 8)
-    k_conv<DIM, OUT, 8><<<blocks, 256, 0, s>>>(g, in, w, bias, out, mask, skip1, skip2);
-  else
-    k_conv<DIM, OUT, 16><<<blocks, 256, 0, s>>>(g, in, w, bias, out, mask, skip1, skip2);
-}
-
-// Weight / bias gradient partials of one layer: for every tap
-//   dW[tap][ci][co] = sum_p act[p + off(tap)][ci] * dz[p][co],  db[co] = sum_p dz[p][co]
-// Each block covers a strided set of 16-point chunks and writes TAPS*256+16
-// FP32 partials.  The 16 rows of an MFMA tile are (tap, ci) pairs: one tap
-// of 16 input channels, two taps of 8 or four of 4 (CG), so a layer with
-// few input channels needs fewer tiles.
-template <int DIM, int CG = kCP>
-__global__ __launch_bounds__(256) void k_wgrad(CnnGeom g, const uint16_t* __restrict__ act,
-                                               const uint16_t* __restrict__ dz,
-                                               float* __restrict__ part) {
-  constexpr int TAPS = DIM == 2 ? 9 : 27;
-  constexpr int NP = TAPS * 256 + 16;
-  static_assert(CG == 16 || CG == 8 || CG == 4, "channel group");
-  constexpr int TPM = kCP / CG;                 // taps per tile
-  constexpr int NT = (TAPS + TPM - 1) / TPM;    // tiles
-  __shared__ float red[NP];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int m = lane & 15, kg = lane >> 4;
-  // the lane's A row m: tap t * TPM + msub, input channel mc
-  const int msub = m / CG, mc = m % CG;
-  f32x4 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float db = 0.f;
-  const long nchunks = (g.P + 15) / 16;
-  const long nw = (long)gridDim.x * 4;
-  for (long c = (long)blockIdx.x * 4 + wv; c < nchunks; c += nw) {
-    const long p0 = c * 16;
-    bf16x4 b;
-    long pq[4];
-    int ci[4], cj[4], ck[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      pq[q] = p0 + 4 * kg + q;
-      if (pq[q] < g.P) {
-        b[q] = (short)dz[pq[q] * kCP + m];
-        coords(g, pq[q], ci[q], cj[q], ck[q]);
-      } else {
-        b[q] = 0;
-        ci[q] = cj[q] = ck[q] = 0;
-      }
-      db += bf2f((uint16_t)b[q]);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int tap = t * TPM + msub;
-      int dx, dy, dzz;
-      tap_off(tap, DIM, dx, dy, dzz);
-      bf16x4 a;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[q] = 0;
-        if (tap < TAPS && pq[q] < g.P) {
-          const long n = nb_index(g, pq[q], ci[q], cj[q], ck[q], dx, dy, dzz);
-          if (n >= 0) a[q] = (short)act[n * kCP + mc];
-        }
-      }
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
-    }
-  }
-  __shared__ float dbs[256];
-  for (int e = threadIdx.x; e < NP; e += 256) red[e] = 0.f;
-  dbs[threadIdx.x] = db;  // slot (wave, kg, m)
-  __syncthreads();
-  // waves add their tiles in a fixed order: D[row 4kg+q][co = m], row =
-  // (tap t * TPM + row / CG, ci = row % CG); every barrier below is reached
-  // by all waves
-  for (int w = 0; w < 4; ++w) {
-    if (wv == w) {
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int row = 4 * kg + q, tap = t * TPM + row / CG;
-          if (tap < TAPS) red[tap * 256 + (row % CG) * 16 + m] += acc[t][q];
-        }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x < 16) {
-    float s = 0.f;
-    for (int e = 0; e < 16; ++e) s += dbs[(e >> 2) * 64 + (e & 3) * 16 + threadIdx.x];
-    red[TAPS * 256 + threadIdx.x] = s;
-  }
-  __syncthreads();
-  float* dst = part + (size_t)blockIdx.x * NP;
-  for (int e = threadIdx.x; e < NP; e += 256) dst[e] = red[e];
-}
-
-// Sum the block partials in a fixed order: a block takes 16 consecutive
-// outputs; its 16 thread groups sum the partials b = g, g + 16, ... of
-// them, and the 16 group sums are added in order.
-constexpr int kRedOut = 16;
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int nblk,
-                                                      int np, float* __restrict__ out) {
-  const int o = threadIdx.x % kRedOut, grp = threadIdx.x / kRedOut;
-  const int e = blockIdx.x * kRedOut + o;
-  float s = 0.f;
-  if (e < np)
-    for (int b = grp; b < nblk; b += 256 / kRedOut) s += part[(size_t)b * np + e];
-  __shared__ float sh[256];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  if (grp == 0 && e < np) {
-    float t = 0.f;
-    for (int g = 0; g < 256 / kRedOut; ++g) t += sh[g * kRedOut + o];
-    out[e] = t;
-  }
-}
-
-// padded gradient [taps][ci][co] + db[co] -> flat layer layout W[tap][ci][co], b[co]
-__global__ __launch_bounds__(256) void k_grad_flat(const float* __restrict__ pad, int taps, int cin,
-                                                   int cout, float* __restrict__ flat) {
-  const int n = taps * cin * cout + cout;
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < n; e += gridDim.x * 256) {
-    if (e < taps * cin * cout) {
-      const int co = e % cout, ci = (e / cout) % cin, t = e / (cout * cin);
-      flat[e] = pad[t * 256 + ci * 16 + co];
-    } else {
-      flat[e] = pad[taps * 256 + (e - taps * cin * cout)];
-    }
-  }
-}
 
 // flat FP32 layer parameters -> BF16 forward weights wf[t][co][ci], dgrad
 // weights wd[t][ci][co] taken from the mirrored tap, FP32 bias[16]
@@ -306,44 +42,16 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
     bias[threadIdx.x] = threadIdx.x < cout ? flat[taps * cin * cout + threadIdx.x] : 0.f;
 }
 
-// FP32 [P][c] -> BF16 [P][16] (zero padding)
-__global__ __launch_bounds__(256) void k_to_act(long P, int c, const float* __restrict__ x,
-                                                uint16_t* __restrict__ a) {
-  for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < P * kCP; e += (long)gridDim.x * 256) {
-    const long p = e / kCP;
-    const int ch = int(e % kCP);
-    a[e] = f2bf(ch < c ? x[p * c + ch] : 0.f);
-  }
-}
-
-// FP32 [P][16] -> FP32 [P][c]
-__global__ __launch_bounds__(256) void k_from16(long P, int c, const float* __restrict__ y16,
-                                                float* __restrict__ y) {
-  for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < P * c; e += (long)gridDim.x * 256)
-    y[e] = y16[(e / c) * kCP + e % c];
-}
-
-// FP32 [P][c] -> BF16 [P][16] gradient seed
-__global__ __launch_bounds__(256) void k_dy_to_bf(long P, int c, const float* __restrict__ dy,
-                                                  uint16_t* __restrict__ d) {
-  for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < P * kCP; e += (long)gridDim.x * 256) {
-    const int ch = int(e % kCP);
-    d[e] = f2bf(ch < c ? dy[(e / kCP) * c + ch] : 0.f);
-  }
-}
-
 // per-sample partial sums of ||y - e||^2 and ||e||^2 (grid: (blocks, batch))
-__global__ __launch_bounds__(256) void k_loss_part(long Pb, int c, const float* __restrict__ y16,
+__global__ __launch_bounds__(256) void k_loss_part(long Pb, int c, const float* __restrict__ y,
                                                    const float* __restrict__ e,
                                                    double* __restrict__ num,
                                                    double* __restrict__ den) {
   const int s = blockIdx.y;
   double a = 0.0, b = 0.0;
   for (long q = (long)blockIdx.x * 256 + threadIdx.x; q < Pb * c; q += (long)gridDim.x * 256) {
-    const long p = q / c;
-    const int ch = int(q % c);
     const double ev = e[(size_t)s * Pb * c + q];
-    const double d = double(y16[((size_t)s * Pb + p) * kCP + ch]) - ev;
+    const double d = double(y[(size_t)s * Pb * c + q]) - ev;
     a += d * d;
     b += ev * ev;
   }
@@ -377,21 +85,22 @@ __global__ __launch_bounds__(256) void k_loss_final(int batch, int nblk, long pe
   if (threadIdx.x == 0) scal[0] = L / batch;
 }
 
-// dz = 2 (y - e) / (points * channels * batch), BF16 [P][16]
+// dz = 2 (y - e) / (points * channels * batch), BF16 [P][chan_group(c)]
 __global__ __launch_bounds__(256) void k_loss_grad(long Pb, int c, int batch,
-                                                   const float* __restrict__ y16,
+                                                   const float* __restrict__ y,
                                                    const float* __restrict__ e,
                                                    const double* __restrict__ scal,
                                                    uint16_t* __restrict__ dz) {
+  const int cg = chan_group(c);
   const long P = Pb * batch;
-  for (long q = (long)blockIdx.x * 256 + threadIdx.x; q < P * kCP; q += (long)gridDim.x * 256) {
-    const long p = q / kCP;
-    const int ch = int(q % kCP);
+  for (long q = (long)blockIdx.x * 256 + threadIdx.x; q < P * cg; q += (long)gridDim.x * 256) {
+    const long p = q / cg;
+    const int ch = int(q % cg);
     float v = 0.f;
     if (ch < c) {
       const int s = int(p / Pb);
       const double ev = e[p * c + ch];
-      v = float(2.0 * (double(y16[q]) - ev) * scal[1 + s] / batch);
+      v = float(2.0 * (double(y[p * c + ch]) - ev) * scal[1 + s] / batch);
     }
     dz[q] = f2bf(v);
   }
@@ -411,7 +120,7 @@ __global__ __launch_bounds__(256) void k_adam(int n, float* __restrict__ w,
   }
 }
 
-// gather crops: inputs [pairs][P][cin] -> act BF16 [B][crop^d][16],
+// gather crops: inputs [pairs][P][cin] -> act BF16 [B][crop^d][chan_group(cin)],
 // targets [pairs][P][cout] -> e FP32 [B][crop^d][cout]; desc[s] = {pair, ox, oy, oz}
 __global__ __launch_bounds__(256) void k_gather(int nx, int ny, int nz, int dim, int crop, int cin,
                                                 int cout, const float* __restrict__ inputs,
@@ -427,8 +136,9 @@ __global__ __launch_bounds__(256) void k_gather(int nx, int ny, int nz, int dim,
     const int i = int(q % crop), j = int((q / crop) % crop), k = int(q / ((long)crop * crop));
     const long src = ((long)(k + oz) * ny + (j + oy)) * nx + (i + ox);
     const float* xi = inputs + ((size_t)pair * P + src) * cin;
-    uint16_t* a = act + ((size_t)s * Pc + q) * kCP;
-    for (int ch = 0; ch < kCP; ++ch) a[ch] = f2bf(ch < cin ? xi[ch] : 0.f);
+    const int cg = chan_group(cin);
+    uint16_t* a = act + ((size_t)s * Pc + q) * cg;
+    for (int ch = 0; ch < cg; ++ch) a[ch] = f2bf(ch < cin ? xi[ch] : 0.f);
     const float* ti = targets + ((size_t)pair * P + src) * cout;
     float* eo = e + ((size_t)s * Pc + q) * cout;
     for (int ch = 0; ch < cout; ++ch) eo[ch] = ti[ch];
@@ -450,12 +160,11 @@ struct gkb_cnn {
   int adam_t = 0;
   // workspace (grown on demand)
   long cap = 0;
-  uint16_t* act[gkb::kMaxLayers] = {nullptr};
+  uint16_t* act[gkb::kMaxLayers] = {nullptr};  // layer inputs, [P][chan_group]
   uint16_t *dz0 = nullptr, *dz1 = nullptr;
-  float* y16 = nullptr;
-  float* pad = nullptr;    // padded grad of one layer
+  float* y = nullptr;      // output [P][c_L]
   float* wpart = nullptr;  // wgrad block partials
-  int wblk = 0;
+  size_t wcap = 0;
   double* lscal = nullptr;  // loss scalars
   double *lnum = nullptr, *lden = nullptr;
   int lcap = 0;
@@ -500,91 +209,89 @@ int cnn_prepare_weights(gkb_cnn* n) {
 }
 
 int cnn_reserve(gkb_cnn* n, long P) {
-  // point indices are decomposed in 32-bit arithmetic (coords)
+  // tiles of points are counted in 32 bits
   if (P <= 0 || P > 0x7fffffffL) return GKB_EINVAL;
   if (P <= n->cap) return GKB_OK;
-  for (int l = 0; l < n->L; ++l) {
-    if (n->act[l]) (void)hipFree(n->act[l]);
-    CNNCK(hipMalloc(&n->act[l], P * gkb::kCP * sizeof(uint16_t)));
-  }
-  if (n->dz0) (void)hipFree(n->dz0);
-  if (n->dz1) (void)hipFree(n->dz1);
-  if (n->y16) (void)hipFree(n->y16);
-  CNNCK(hipMalloc(&n->dz0, P * gkb::kCP * sizeof(uint16_t)));
-  CNNCK(hipMalloc(&n->dz1, P * gkb::kCP * sizeof(uint16_t)));
-  CNNCK(hipMalloc(&n->y16, P * gkb::kCP * sizeof(float)));
+  n->cap = 0;
+  auto grow = [&](auto*& p, size_t bytes) {
+    if (p) (void)hipFree(p);
+    p = nullptr;
+    return hipMalloc(&p, bytes);
+  };
+  int cmax = 1;
+  for (int l = 0; l <= n->L; ++l) cmax = std::max(cmax, n->ch[l]);
+  for (int l = 0; l < n->L; ++l)
+    CNNCK(grow(n->act[l], P * gkb::chan_group(n->ch[l]) * sizeof(uint16_t)));
+  CNNCK(grow(n->dz0, P * gkb::chan_group(cmax) * sizeof(uint16_t)));
+  CNNCK(grow(n->dz1, P * gkb::chan_group(cmax) * sizeof(uint16_t)));
+  CNNCK(grow(n->y, P * n->ch[n->L] * sizeof(float)));
   n->cap = P;
   return GKB_OK;
 }
 
-template <int DIM>
-void cnn_forward_dim(gkb_cnn* n, const gkb::CnnGeom& g) {
-  const int blocks = gkb::conv_blocks(g.P);
+// the BF16 input of the network that a caller filled
+gkb::ConvIn cnn_act0(const gkb_cnn* n) { return gkb::ConvIn{n->act[0], n->ch[0], false}; }
+
+// hidden layers from the input x, then (y != null) the output layer into y
+// (FP32 [P][c_L]); skip1, skip2 as conv_layer
+void cnn_layers(hipStream_t s, const gkb_cnn* n, const gkb::CnnGeom& g, const gkb::ConvIn& x,
+                float* y, const int* skip1 = nullptr, const int* skip2 = nullptr) {
+  gkb::ConvIn in = x;
   for (int l = 0; l < n->L; ++l) {
     const uint16_t* w = n->wf + (size_t)l * n->taps * 256;
     const float* b = n->bias + 16 * l;
-    if (l < n->L - 1)
-      gkb::launch_conv<DIM, gkb::kOutReluBf16>(n->ch[l], blocks, n->s, g, n->act[l], w, b,
-                                               n->act[l + 1], nullptr);
-    else
-      gkb::launch_conv<DIM, gkb::kOutF32>(n->ch[l], blocks, n->s, g, n->act[l], w, b, n->y16,
-                                          nullptr);
+    const int cout = n->ch[l + 1];
+    if (l < n->L - 1) {
+      gkb::conv_layer(s, n->dim, g, in, w, b, gkb::kOutReluBf16, n->act[l + 1], cout, nullptr,
+                      skip1, skip2);
+      in = gkb::ConvIn{n->act[l + 1], cout, false};
+    } else if (y) {
+      gkb::conv_layer(s, n->dim, g, in, w, b, gkb::kOutF32, y, cout, nullptr, skip1, skip2);
+    }
   }
 }
 
-// forward from n->act[0] (already filled) into n->y16
-int cnn_forward_act(gkb_cnn* n, const gkb::CnnGeom& g) {
+int cnn_forward(gkb_cnn* n, const gkb::CnnGeom& g, const gkb::ConvIn& x, float* y) {
   int rc = cnn_prepare_weights(n);
   if (rc) return rc;
-  if (n->dim == 2) cnn_forward_dim<2>(n, g);
-  else cnn_forward_dim<3>(n, g);
+  cnn_layers(n->s, n, g, x, y);
   CNNCK(hipGetLastError());
   return GKB_OK;
 }
 
-template <int DIM>
-int cnn_backward_dim(gkb_cnn* n, const gkb::CnnGeom& g, float* dx16) {
-  constexpr int TAPS = DIM == 2 ? 9 : 27;
-  const int NP = TAPS * 256 + 16;
-  const int wblk = (int)std::max<long>(1, std::min<long>((g.P + 1023) / 1024, 512));
-  if (wblk > n->wblk) {
+// parameter gradient into n->grad and (dx != null) the input gradient, from
+// the hidden activations of cnn_forward, its input x and the output gradient
+int cnn_backward(gkb_cnn* n, const gkb::CnnGeom& g, const gkb::ConvIn& x, const gkb::ConvIn& dy,
+                 float* dx) {
+  int rc = cnn_prepare_weights(n);
+  if (rc) return rc;
+  const size_t need = gkb::wgrad_part_floats(n->dim, g);
+  if (need > n->wcap) {
     if (n->wpart) (void)hipFree(n->wpart);
-    CNNCK(hipMalloc(&n->wpart, (size_t)wblk * NP * sizeof(float)));
-    n->wblk = wblk;
+    n->wpart = nullptr;
+    n->wcap = 0;
+    CNNCK(hipMalloc(&n->wpart, need * sizeof(float)));
+    n->wcap = need;
   }
-  const int blocks = gkb::conv_blocks(g.P);
-  uint16_t* dz = n->dz0;
-  uint16_t* dzn = n->dz1;
+  gkb::ConvIn dz = dy;
+  // dz0 may hold the output gradient: the hidden ones start in dz1
+  uint16_t *cur = n->dz1, *other = n->dz0;
   for (int l = n->L - 1; l >= 0; --l) {
-    if (n->ch[l] <= 4)
-      gkb::k_wgrad<DIM, 4><<<wblk, 256, 0, n->s>>>(g, n->act[l], dz, n->wpart);
-    else if (n->ch[l] <= 8)
-      gkb::k_wgrad<DIM, 8><<<wblk, 256, 0, n->s>>>(g, n->act[l], dz, n->wpart);
-    else
-      gkb::k_wgrad<DIM, 16><<<wblk, 256, 0, n->s>>>(g, n->act[l], dz, n->wpart);
-    gkb::k_wgrad_reduce<<<(NP + gkb::kRedOut - 1) / gkb::kRedOut, 256, 0, n->s>>>(n->wpart, wblk,
-                                                                                 NP, n->pad);
-    gkb::k_grad_flat<<<cnn_grid(TAPS * 256 + 16), 256, 0, n->s>>>(n->pad, TAPS, n->ch[l],
-                                                                   n->ch[l + 1], n->grad + n->off[l]);
-    const uint16_t* wd = n->wd + (size_t)l * TAPS * 256;
+    const gkb::ConvIn a = l == 0 ? x : gkb::ConvIn{n->act[l], n->ch[l], false};
+    gkb::wgrad_layer(n->s, n->dim, g, a, dz, n->wpart, n->grad + n->off[l]);
+    const uint16_t* wd = n->wd + (size_t)l * n->taps * 256;
     // the adjoint convolution reads the layer's output channels
     if (l > 0) {
-      gkb::launch_conv<DIM, gkb::kOutMaskBf16>(n->ch[l + 1], blocks, n->s, g, dz, wd, nullptr,
-                                               dzn, n->act[l]);
-      std::swap(dz, dzn);
-    } else if (dx16) {
-      gkb::launch_conv<DIM, gkb::kOutF32>(n->ch[l + 1], blocks, n->s, g, dz, wd, nullptr, dx16,
-                                          nullptr);
+      gkb::conv_layer(n->s, n->dim, g, dz, wd, nullptr, gkb::kOutMaskBf16, cur, n->ch[l],
+                      n->act[l]);
+      dz = gkb::ConvIn{cur, n->ch[l], false};
+      std::swap(cur, other);
+    } else if (dx) {
+      gkb::conv_layer(n->s, n->dim, g, dz, wd, nullptr, gkb::kOutF32, dx, n->ch[0], nullptr);
     }
   }
   CNNCK(hipGetLastError());
   return GKB_OK;
-}
-
-int cnn_backward_act(gkb_cnn* n, const gkb::CnnGeom& g, float* dx16) {
-  int rc = cnn_prepare_weights(n);
-  if (rc) return rc;
-  return n->dim == 2 ? cnn_backward_dim<2>(n, g, dx16) : cnn_backward_dim<3>(n, g, dx16);
 }
 
 int cnn_adam(gkb_cnn* n, double lr, double b1, double b2, double eps) {
@@ -642,8 +349,7 @@ int gkb_cnn_create(int dim, int n_layers, const int* channels, unsigned seed, gk
   }
   if (hipMalloc(&n->wf, (size_t)n_layers * n->taps * 256 * 2) != hipSuccess ||
       hipMalloc(&n->wd, (size_t)n_layers * n->taps * 256 * 2) != hipSuccess ||
-      hipMalloc(&n->bias, (size_t)n_layers * 16 * 4) != hipSuccess ||
-      hipMalloc(&n->pad, (size_t)(27 * 256 + 16) * 4) != hipSuccess)
+      hipMalloc(&n->bias, (size_t)n_layers * 16 * 4) != hipSuccess)
     return fail(GKB_ENOMEM);
   // seeded He-uniform initialisation (64-bit LCG), zero biases
   std::vector<float> h(n->np, 0.f);
@@ -668,8 +374,8 @@ void gkb_cnn_destroy(gkb_cnn* n) {
   if (!n) return;
   if (n->s) (void)hipStreamSynchronize(n->s);
   void* ptrs[] = {n->params, n->grad, n->m,    n->v,    n->wf,    n->wd,   n->bias,
-                  n->dz0,    n->dz1,  n->y16,  n->pad,  n->wpart, n->lscal, n->lnum,
-                  n->lden,   n->ebuf, n->desc};
+                  n->dz0,    n->dz1,  n->y,    n->wpart, n->lscal, n->lnum, n->lden,
+                  n->ebuf,   n->desc};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int l = 0; l < gkb::kMaxLayers; ++l)
@@ -701,10 +407,8 @@ int gkb_cnn_forward(gkb_cnn* n, int nx, int ny, int nz, int batch, const float* 
   gkb::CnnGeom g{nx, ny, nz, batch, (long)nx * ny * nz * batch};
   int rc = cnn_reserve(n, g.P);
   if (rc) return rc;
-  gkb::k_to_act<<<cnn_grid(g.P * 16), 256, 0, n->s>>>(g.P, n->ch[0], x, n->act[0]);
-  rc = cnn_forward_act(n, g);
+  rc = cnn_forward(n, g, gkb::ConvIn{x, n->ch[0], true}, y);
   if (rc) return rc;
-  gkb::k_from16<<<cnn_grid(g.P * n->ch[n->L]), 256, 0, n->s>>>(g.P, n->ch[n->L], n->y16, y);
   CNNCK(hipStreamSynchronize(n->s));
   return GKB_OK;
 }
@@ -718,15 +422,11 @@ int gkb_cnn_backward(gkb_cnn* n, int nx, int ny, int nz, int batch, const float*
   gkb::CnnGeom g{nx, ny, nz, batch, (long)nx * ny * nz * batch};
   int rc = cnn_reserve(n, g.P);
   if (rc) return rc;
-  gkb::k_to_act<<<cnn_grid(g.P * 16), 256, 0, n->s>>>(g.P, n->ch[0], x, n->act[0]);
-  rc = cnn_forward_act(n, g);
+  const gkb::ConvIn in{x, n->ch[0], true};
+  rc = cnn_forward(n, g, in, nullptr);  // the output itself is not needed
   if (rc) return rc;
-  gkb::k_dy_to_bf<<<cnn_grid(g.P * 16), 256, 0, n->s>>>(g.P, n->ch[n->L], dy, n->dz0);
-  float* dx16 = nullptr;
-  if (dx) dx16 = n->y16;  // the forward output is no longer needed
-  rc = cnn_backward_act(n, g, dx16);
+  rc = cnn_backward(n, g, in, gkb::ConvIn{dy, n->ch[n->L], true}, dx);
   if (rc) return rc;
-  if (dx) gkb::k_from16<<<cnn_grid(g.P * n->ch[0]), 256, 0, n->s>>>(g.P, n->ch[0], dx16, dx);
   if (grad_host) CNNCK(hipMemcpyAsync(grad_host, n->grad, n->np * 4, hipMemcpyDeviceToHost, n->s));
   CNNCK(hipStreamSynchronize(n->s));
   return GKB_OK;
@@ -785,14 +485,14 @@ int gkb_cnn_train(gkb_cnn* n, const float* inputs, const float* targets, int n_p
     CNNCK(hipMemcpyAsync(n->desc, desc.data(), 4 * batch * sizeof(int), hipMemcpyHostToDevice, n->s));
     gkb::k_gather<<<dim3(cnn_grid(Pc), batch), 256, 0, n->s>>>(
         nx, ny, nz, dim, crop, cin, cout, inputs, targets, n->desc, n->act[0], n->ebuf);
-    rc = cnn_forward_act(n, g);
+    rc = cnn_forward(n, g, cnn_act0(n), n->y);
     if (rc) return rc;
-    gkb::k_loss_part<<<dim3(lblk, batch), 256, 0, n->s>>>(Pc, cout, n->y16, n->ebuf, n->lnum,
+    gkb::k_loss_part<<<dim3(lblk, batch), 256, 0, n->s>>>(Pc, cout, n->y, n->ebuf, n->lnum,
                                                           n->lden);
     gkb::k_loss_final<<<1, 256, 0, n->s>>>(batch, lblk, Pc * cout, n->lnum, n->lscal);
-    gkb::k_loss_grad<<<cnn_grid(g.P * 16), 256, 0, n->s>>>(Pc, cout, batch, n->y16, n->ebuf,
+    gkb::k_loss_grad<<<cnn_grid(g.P * 4), 256, 0, n->s>>>(Pc, cout, batch, n->y, n->ebuf,
                                                            n->lscal, n->dz0);
-    rc = cnn_backward_act(n, g, nullptr);
+    rc = cnn_backward(n, g, cnn_act0(n), gkb::ConvIn{n->dz0, cout, false}, nullptr);
     if (rc) return rc;
     rc = cnn_adam(n, lr, 0.9, 0.999, 1e-8);
     if (rc) return rc;
@@ -822,11 +522,9 @@ int gkb_cnn_eval(gkb_cnn* n, const float* inputs, const float* targets, int n_pa
   if (rc) return rc;
   double total = 0.0, hl[1];
   for (int k = 0; k < n_pairs; ++k) {
-    gkb::k_to_act<<<cnn_grid(P * 16), 256, 0, n->s>>>(P, cin, inputs + (size_t)k * P * cin,
-                                                      n->act[0]);
-    rc = cnn_forward_act(n, g);
+    rc = cnn_forward(n, g, gkb::ConvIn{inputs + (size_t)k * P * cin, cin, true}, n->y);
     if (rc) return rc;
-    gkb::k_loss_part<<<dim3(lblk, 1), 256, 0, n->s>>>(P, cout, n->y16,
+    gkb::k_loss_part<<<dim3(lblk, 1), 256, 0, n->s>>>(P, cout, n->y,
                                                       targets + (size_t)k * P * cout, n->lnum,
                                                       n->lden);
     gkb::k_loss_final<<<1, 256, 0, n->s>>>(1, lblk, P * cout, n->lnum, n->lscal);

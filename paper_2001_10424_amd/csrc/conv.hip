@@ -1,0 +1,444 @@
+// Convolutions of the preconditioner network as implicit GEMMs on
+// v_mfma_f32_16x16x32_bf16 (see conv.hpp).
+//
+// A block stages the input of a tile of points with its one-point halo in LDS
+// once (zeros outside the grid), so a tap is an LDS read at a fixed offset
+// instead of a gather from memory with its own address and bounds.  32 values
+// of the GEMM's K dimension are two taps of 16 channels, four of 8 or eight
+// of 4.
+#include "conv.hpp"
+
+#include <algorithm>
+
+namespace gkb {
+namespace {
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 256;
+
+// tile of output points: rows of 32 points, 16 rows
+template <int DIM>
+struct CTile {
+  static constexpr int TX = 32, TY = DIM == 3 ? 4 : 16, TZ = DIM == 3 ? 4 : 1;
+  static constexpr int SX = TX + 2, SY = TY + 2, SZ = DIM == 3 ? TZ + 2 : 1;
+  static constexpr int N = SX * SY * SZ;     // staged points
+  static constexpr int TAPS = DIM == 3 ? 27 : 9;
+};
+
+struct TileAt {
+  int x, y, z;  // origin
+  long base;    // first point of the batch entry
+};
+
+template <int DIM>
+__host__ __device__ inline long tile_count(const CnnGeom& g) {
+  typedef CTile<DIM> C;
+  return (long)((g.nx + C::TX - 1) / C::TX) * ((g.ny + C::TY - 1) / C::TY) *
+         ((g.nz + C::TZ - 1) / C::TZ) * g.batch;
+}
+
+template <int DIM>
+__device__ __forceinline__ TileAt tile_at(const CnnGeom& g, unsigned t) {
+  typedef CTile<DIM> C;
+  const unsigned tx = (g.nx + C::TX - 1) / C::TX, ty = (g.ny + C::TY - 1) / C::TY,
+                 tz = (g.nz + C::TZ - 1) / C::TZ;
+  const unsigned a = t / tx, b = a / ty, c = b / tz;
+  TileAt r;
+  r.x = int(t - a * tx) * C::TX;
+  r.y = int(a - b * ty) * C::TY;
+  r.z = int(b - c * tz) * C::TZ;
+  r.base = (long)c * g.nx * g.ny * g.nz;
+  return r;
+}
+
+// CG channels of point q (BF16), from BF16 or FP32 storage
+template <int CG, bool F32>
+__device__ __forceinline__ void load_point(const void* p, int c, long q, uint16_t* v) {
+  if constexpr (!F32) {
+    const s16x4* a = reinterpret_cast<const s16x4*>(static_cast<const uint16_t*>(p) + q * CG);
+#pragma unroll
+    for (int e = 0; e < CG / 4; ++e) *reinterpret_cast<s16x4*>(v + 4 * e) = a[e];
+  } else {
+    const float* a = static_cast<const float*>(p) + q * c;
+    if (CG == 4 && c == 4 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {  // uniform
+      const f32x4 x = *reinterpret_cast<const f32x4*>(a);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = f2bf(x[e]);
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < CG; ++e) v[e] = e < c ? f2bf(a[e]) : uint16_t(0);
+  }
+}
+
+// stage the tile (with halo: HALO 1, without: 0) into sh[point][CG]
+template <int DIM, int CG, bool F32, int HALO>
+__device__ __forceinline__ void stage(const CnnGeom& g, const TileAt& t, const void* p, int c,
+                                      uint16_t* sh) {
+  typedef CTile<DIM> C;
+  constexpr int SX = C::TX + 2 * HALO, SY = C::TY + 2 * HALO, SZ = DIM == 3 ? C::TZ + 2 * HALO : 1;
+  constexpr int N = SX * SY * SZ, PER = (N + kThreads - 1) / kThreads;
+  struct __align__(8) V {
+    uint16_t v[CG];
+  } r[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    const int row = e / SX, x = t.x + e - row * SX - HALO,
+              y = t.y + (DIM == 3 ? row % SY : row) - HALO,
+              z = DIM == 3 ? t.z + row / SY - HALO : 0;
+    const bool in = e < N && unsigned(x) < unsigned(g.nx) && unsigned(y) < unsigned(g.ny) &&
+                    unsigned(z) < unsigned(g.nz);
+    if (in) {
+      load_point<CG, F32>(p, c, t.base + ((long)z * g.ny + y) * g.nx + x, r[q].v);
+    } else {
+#pragma unroll
+      for (int k = 0; k < CG; ++k) r[q].v[k] = 0;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    if (e < N)
+#pragma unroll
+      for (int k = 0; k < CG / 4; ++k)
+        *reinterpret_cast<s16x4*>(sh + e * CG + 4 * k) =
+            *reinterpret_cast<const s16x4*>(r[q].v + 4 * k);
+  }
+}
+
+// LDS offset (in points of the halo box) of tap t seen from the point that
+// the box stores at (x + 1, y + 1, z + 1)
+template <int DIM>
+__device__ __forceinline__ int tap_offset(int t) {
+  typedef CTile<DIM> C;
+  const int dx = t % 3, dy = (t / 3) % 3, dz = DIM == 3 ? t / 9 : 0;
+  return (dz * C::SY + dy) * C::SX + dx;
+}
+
+// The A operand (rows = output channels) is the weights, kept in registers
+// for the whole block; the B operand (columns = points) comes from LDS, 16
+// bytes per lane and MFMA; a lane ends up with four consecutive channels of
+// one point, an 8-byte store.
+// Bound: LDS reads of the B operand, 1 KB per MFMA, and the staging in front
+// of them.  128^3, 4 -> 8 -> 8 -> 3 channels: 34 + 31 + 29 us; 104 + 194 + 198
+// us with per-tap gathers on activations padded to 16 channels, plus 71 us of
+// conversions to and from that padding.
+template <int DIM, int CG, bool F32, int OUT>
+__global__ __launch_bounds__(kThreads) void k_conv(CnnGeom g, const void* __restrict__ in, int cin,
+                                                   const uint16_t* __restrict__ w,
+                                                   const float* __restrict__ bias,
+                                                   void* __restrict__ out, int cout,
+                                                   const uint16_t* __restrict__ mask,
+                                                   const int* __restrict__ skip1,
+                                                   const int* __restrict__ skip2) {
+  typedef CTile<DIM> C;
+  if ((skip1 && *skip1) || (skip2 && *skip2)) return;
+  constexpr int TPM = 32 / CG;                       // taps per MFMA
+  constexpr int NM = (C::TAPS + TPM - 1) / TPM;      // MFMAs per 16 points
+  __shared__ __align__(16) uint16_t sh[C::N * CG];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int m = lane & 15, kg = lane >> 4;
+  const TileAt t = tile_at<DIM>(g, blockIdx.x);
+  // the lane's eight K values of MFMA j: CG >= 8: tap t0, channels c0 ..;
+  // CG = 4: taps t0 and t0 + 1
+  s16x8 wr[NM];
+  int off[NM], off1[NM];
+#pragma unroll
+  for (int j = 0; j < NM; ++j) {
+    const int t0 = CG == 16 ? 2 * j + (kg >> 1) : (CG == 8 ? 4 * j + kg : 8 * j + 2 * kg);
+    const int c0 = CG == 16 ? 8 * (kg & 1) : 0;
+    s16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+    if constexpr (CG >= 8) {
+      if (t0 < C::TAPS) v = *reinterpret_cast<const s16x8*>(w + t0 * 256 + m * 16 + c0);
+      off[j] = t0 < C::TAPS ? tap_offset<DIM>(t0) * CG + c0 : -1;
+      off1[j] = 0;
+    } else {
+      s16x4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
+      if (t0 < C::TAPS) a = *reinterpret_cast<const s16x4*>(w + t0 * 256 + m * 16);
+      if (t0 + 1 < C::TAPS) b = *reinterpret_cast<const s16x4*>(w + (t0 + 1) * 256 + m * 16);
+      v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+      off[j] = t0 < C::TAPS ? tap_offset<DIM>(t0) * CG : -1;
+      off1[j] = t0 + 1 < C::TAPS ? tap_offset<DIM>(t0 + 1) * CG : -1;
+    }
+    wr[j] = v;
+  }
+  f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
+  if (bias) b4 = *reinterpret_cast<const f32x4*>(bias + 4 * kg);
+  const int cgo = chan_group(cout);
+  stage<DIM, CG, F32, 1>(g, t, in, cin, sh);
+  __syncthreads();
+  constexpr int GROUPS = C::TX / 16 * C::TY * C::TZ;
+#pragma unroll 2
+  for (int q = wv; q < GROUPS; q += kThreads / 64) {
+    const int lx = (q & 1) * 16 + m, ly = (q >> 1) % C::TY, lz = (q >> 1) / C::TY;
+    const uint16_t* src = sh + ((lz * C::SY + ly) * C::SX + lx) * CG;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NM; ++j) {
+      s16x8 v;
+      // only the last MFMA can run past the taps: those K values are 0
+      if constexpr (CG >= 8) {
+        v = *reinterpret_cast<const s16x8*>(src + (off[j] < 0 ? 0 : off[j]));
+        if (j == NM - 1 && off[j] < 0) v = s16x8{0, 0, 0, 0, 0, 0, 0, 0};
+      } else {
+        s16x4 a = *reinterpret_cast<const s16x4*>(src + (off[j] < 0 ? 0 : off[j]));
+        s16x4 b = *reinterpret_cast<const s16x4*>(src + (off1[j] < 0 ? 0 : off1[j]));
+        if (j == NM - 1 && off[j] < 0) a = s16x4{0, 0, 0, 0};
+        if (j == NM - 1 && off1[j] < 0) b = s16x4{0, 0, 0, 0};
+        v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[j]),
+                                                    __builtin_bit_cast(bf16x8, v), acc, 0, 0, 0);
+    }
+    // acc[e] = channel 4 kg + e of point m of the group
+    const int x = t.x + lx, y = t.y + ly, z = t.z + lz;
+    if (x >= g.nx || y >= g.ny || z >= g.nz) continue;
+    const long p = t.base + ((long)z * g.ny + y) * g.nx + x;
+    if constexpr (OUT == kOutF32) {
+      float* o = static_cast<float*>(out) + p * cout;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * kg + e < cout) o[4 * kg + e] = acc[e] + b4[e];
+    } else if (4 * kg < cgo) {
+      s16x4 h, mk = {0, 0, 0, 0};
+      if (OUT == kOutMaskBf16) mk = *reinterpret_cast<const s16x4*>(mask + p * cgo + 4 * kg);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v = acc[e] + b4[e];
+        const bool pos = OUT == kOutReluBf16 ? v > 0.f : mk[e] > 0;  // sign bit: <= 0
+        h[e] = pos && 4 * kg + e < cout ? short(f2bf(v)) : short(0);
+      }
+      *reinterpret_cast<s16x4*>(static_cast<uint16_t*>(out) + p * cgo + 4 * kg) = h;
+    }
+  }
+}
+
+// four consecutive 16-bit values along the first index of a matrix stored
+// with rows of 16-bit elements in LDS: the 16 lanes of a quarter wave give the
+// 8-byte pieces of four rows, lane i piece i % 4 of row i / 4, and lane i gets
+// column i of the four rows
+__device__ __forceinline__ s16x4 lds_transposed(const uint16_t* a) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4*)(const_cast<uint16_t*>(a)));
+}
+
+// Weight gradient: a GEMM over points.  The rows of an accumulator tile are
+// (tap, ci) pairs (one tap of 16 input channels, two of 8 or four of 4), its
+// columns the output channels, its K dimension 32 points of a row.  Both
+// operands need consecutive points per lane while LDS holds points by
+// channels, which the transposing LDS read resolves; a tap is an offset of
+// whole points, so it stays aligned.  One more tile with a row of ones gives
+// the bias gradient.  A block sums several tiles of points and writes one set
+// of FP32 partials; k_wgrad_reduce adds the sets in a fixed order.
+// 64^3 x 2 points: 14 us for 8 x 8 channels and 12 us for 4 x 8; 235 and 142
+// us with single BF16 values gathered from memory.
+template <int DIM, int CG>
+constexpr int wgrad_tiles() { return (CTile<DIM>::TAPS * CG + 15) / 16; }
+
+template <int DIM, int CG, int CGZ, bool FA, bool FZ>
+__global__ __launch_bounds__(kThreads) void k_wgrad(CnnGeom g, const void* __restrict__ act, int ca,
+                                                    const void* __restrict__ dz, int cz,
+                                                    float* __restrict__ part) {
+  typedef CTile<DIM> C;
+  constexpr int NT = wgrad_tiles<DIM, CG>(), TPT = 16 / CG;  // taps per tile
+  constexpr int NZ = C::TX * C::TY * C::TZ;
+  constexpr int NR = (NT + 1) * 256;
+  constexpr int BYTES = (C::N * CG + NZ * CGZ) * 2;
+  __shared__ __align__(16) char raw[BYTES > NR * 4 ? BYTES : NR * 4];
+  uint16_t* sa = reinterpret_cast<uint16_t*>(raw);
+  uint16_t* sz = sa + C::N * CG;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int i = lane & 15, kg = lane >> 4;
+  const int piece = i & 3, row = i >> 2;
+  // LDS offset of the lane's piece of tile t, relative to its point
+  int off[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int tap = std::min(t * TPT + (CG == 16 ? 0 : (CG == 8 ? piece >> 1 : piece)), C::TAPS - 1);
+    const int ch = CG == 16 ? 4 * piece : (CG == 8 ? 4 * (piece & 1) : 0);
+    off[t] = tap_offset<DIM>(tap) * CG + ch;
+  }
+  const int zch = 4 * (piece % (CGZ / 4));  // columns beyond the group are not used
+  f32x4 acc[NT + 1];
+#pragma unroll
+  for (int t = 0; t <= NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  s16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = short(0x3F80);
+  const unsigned tiles = unsigned(tile_count<DIM>(g));
+  for (unsigned tl = blockIdx.x; tl < tiles; tl += gridDim.x) {
+    const TileAt t = tile_at<DIM>(g, tl);
+    __syncthreads();  // the last tile's reads
+    stage<DIM, CG, FA, 1>(g, t, act, ca, sa);
+    stage<DIM, CGZ, FZ, 0>(g, t, dz, cz, sz);
+    __syncthreads();
+    for (int r = wv; r < C::TY * C::TZ; r += kThreads / 64) {
+      const int ly = r % C::TY, lz = r / C::TY;
+      // K values of the lane: points 8 kg + 0 .. 7 of the row
+      const int x = 8 * kg + row;
+      const uint16_t* pz = sz + (r * C::TX + x) * CGZ + zch;
+      const s16x4 z0 = lds_transposed(pz), z1 = lds_transposed(pz + 4 * CGZ);
+      const s16x8 zv = __builtin_shufflevector(z0, z1, 0, 1, 2, 3, 4, 5, 6, 7);
+      const uint16_t* pa = sa + ((lz * C::SY + ly) * C::SX + x) * CG;
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        const s16x4 a0 = lds_transposed(pa + off[q]), a1 = lds_transposed(pa + off[q] + 4 * CG);
+        const s16x8 av = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
+        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
+                                                         __builtin_bit_cast(bf16x8, zv), acc[q], 0,
+                                                         0, 0);
+      }
+      acc[NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones),
+                                                        __builtin_bit_cast(bf16x8, zv), acc[NT], 0,
+                                                        0, 0);
+    }
+  }
+  // the waves add their tiles in a fixed order
+  float* red = reinterpret_cast<float*>(raw);
+  for (int w = 0; w < kThreads / 64; ++w) {
+    __syncthreads();
+    if (wv == w)
+#pragma unroll
+      for (int t = 0; t <= NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float* d = red + t * 256 + (4 * kg + q) * 16 + i;
+          *d = w == 0 ? acc[t][q] : *d + acc[t][q];
+        }
+  }
+  __syncthreads();
+  float* dst = part + (size_t)blockIdx.x * NR;
+  for (int e = threadIdx.x; e < NR; e += kThreads) dst[e] = red[e];
+}
+
+// Sum the block partials in a fixed order into the flat layer gradient
+// W[tap][ci][co], b[co]: a block takes 16 consecutive partial entries, its 16
+// thread groups sum the sets b = grp, grp + 16, ..., and the 16 group sums are
+// added in order.
+constexpr int kRedOut = 16;
+__global__ __launch_bounds__(kThreads) void k_wgrad_reduce(const float* __restrict__ part, int nblk,
+                                                           int nt, int cg, int taps, int cin,
+                                                           int cout, float* __restrict__ flat) {
+  const int o = threadIdx.x % kRedOut, grp = threadIdx.x / kRedOut;
+  const int np = (nt + 1) * 256, e = blockIdx.x * kRedOut + o;
+  float s = 0.f;
+#pragma unroll 8
+  for (int b = grp; b < nblk; b += kThreads / kRedOut) s += part[(size_t)b * np + e];
+  __shared__ float sh[kThreads];
+  sh[threadIdx.x] = s;
+  __syncthreads();
+  if (grp != 0) return;
+  float t = 0.f;
+  for (int q = 0; q < kThreads / kRedOut; ++q) t += sh[q * kRedOut + o];
+  // entry e: tile, row (tap, ci) of the tile, column co = o
+  const int row = (e >> 4) & 15, tile = e >> 8;
+  if (o >= cout) return;
+  if (tile == nt) {
+    if (row == 0) flat[taps * cin * cout + o] = t;
+    return;
+  }
+  const int tap = tile * (16 / cg) + row / cg, ci = row % cg;
+  if (tap < taps && ci < cin) flat[(tap * cin + ci) * cout + o] = t;
+}
+
+template <int DIM, int CG, bool F32>
+void launch_conv(hipStream_t s, const CnnGeom& g, const ConvIn& in, const uint16_t* w,
+                 const float* bias, ConvOut mode, void* out, int cout, const uint16_t* mask,
+                 const int* skip1, const int* skip2) {
+  const unsigned blocks = unsigned(tile_count<DIM>(g));
+  switch (mode) {
+    case kOutReluBf16:
+      k_conv<DIM, CG, F32, kOutReluBf16><<<blocks, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
+      break;
+    case kOutF32:
+      k_conv<DIM, CG, F32, kOutF32><<<blocks, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
+      break;
+    case kOutMaskBf16:
+      k_conv<DIM, CG, F32, kOutMaskBf16><<<blocks, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
+      break;
+  }
+}
+
+template <int DIM, bool F32>
+void conv_cg(hipStream_t s, const CnnGeom& g, const ConvIn& in, const uint16_t* w,
+             const float* bias, ConvOut mode, void* out, int cout, const uint16_t* mask,
+             const int* skip1, const int* skip2) {
+  const int cg = chan_group(in.c);
+  if (cg == 4) launch_conv<DIM, 4, F32>(s, g, in, w, bias, mode, out, cout, mask, skip1, skip2);
+  else if (cg == 8) launch_conv<DIM, 8, F32>(s, g, in, w, bias, mode, out, cout, mask, skip1, skip2);
+  else launch_conv<DIM, 16, F32>(s, g, in, w, bias, mode, out, cout, mask, skip1, skip2);
+}
+
+template <int DIM, int CG, int CGZ, bool FA>
+void wgrad_fz(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& dz, float* part,
+              int nblk) {
+  if (dz.f32) k_wgrad<DIM, CG, CGZ, FA, true><<<nblk, kThreads, 0, s>>>(g, act.p, act.c, dz.p, dz.c, part);
+  else k_wgrad<DIM, CG, CGZ, FA, false><<<nblk, kThreads, 0, s>>>(g, act.p, act.c, dz.p, dz.c, part);
+}
+
+template <int DIM, int CG>
+void wgrad_cg(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& dz, float* part,
+              float* flat) {
+  const int nblk = wgrad_blocks(DIM, g), cz = chan_group(dz.c);
+  // FP32 activations are the network's input only
+  if (act.f32) {
+    if (cz == 4) wgrad_fz<DIM, CG, 4, true>(s, g, act, dz, part, nblk);
+    else if (cz == 8) wgrad_fz<DIM, CG, 8, true>(s, g, act, dz, part, nblk);
+    else wgrad_fz<DIM, CG, 16, true>(s, g, act, dz, part, nblk);
+  } else {
+    if (cz == 4) wgrad_fz<DIM, CG, 4, false>(s, g, act, dz, part, nblk);
+    else if (cz == 8) wgrad_fz<DIM, CG, 8, false>(s, g, act, dz, part, nblk);
+    else wgrad_fz<DIM, CG, 16, false>(s, g, act, dz, part, nblk);
+  }
+  constexpr int nt = wgrad_tiles<DIM, CG>();
+  k_wgrad_reduce<<<(nt + 1) * 256 / kRedOut, kThreads, 0, s>>>(part, nblk, nt, CG,
+                                                               CTile<DIM>::TAPS, act.c, dz.c, flat);
+}
+
+template <int DIM>
+void wgrad_dim(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& dz, float* part,
+               float* flat) {
+  const int cg = chan_group(act.c);
+  if (cg == 4) wgrad_cg<DIM, 4>(s, g, act, dz, part, flat);
+  else if (cg == 8) wgrad_cg<DIM, 8>(s, g, act, dz, part, flat);
+  else wgrad_cg<DIM, 16>(s, g, act, dz, part, flat);
+}
+
+}  // namespace
+
+void conv_layer(hipStream_t s, int dim, const CnnGeom& g, const ConvIn& in, const uint16_t* w,
+                const float* bias, ConvOut mode, void* out, int cout, const uint16_t* mask,
+                const int* skip1, const int* skip2) {
+  if (dim == 2) {
+    if (in.f32) conv_cg<2, true>(s, g, in, w, bias, mode, out, cout, mask, skip1, skip2);
+    else conv_cg<2, false>(s, g, in, w, bias, mode, out, cout, mask, skip1, skip2);
+  } else {
+    if (in.f32) conv_cg<3, true>(s, g, in, w, bias, mode, out, cout, mask, skip1, skip2);
+    else conv_cg<3, false>(s, g, in, w, bias, mode, out, cout, mask, skip1, skip2);
+  }
+}
+
+// blocks of the weight gradient: two per CU (12-15 us a layer at 64^3 x 2; one
+// per CU takes 16-18 us and saves nothing in the reduction, 4.7 us)
+int wgrad_blocks(int dim, const CnnGeom& g) {
+  const long tiles = dim == 2 ? tile_count<2>(g) : tile_count<3>(g);
+  return int(std::min<long>(tiles, 512));
+}
+
+size_t wgrad_part_floats(int dim, const CnnGeom& g) {
+  const int nt = dim == 2 ? wgrad_tiles<2, 16>() : wgrad_tiles<3, 16>();
+  return (size_t)wgrad_blocks(dim, g) * (nt + 1) * 256;
+}
+
+void wgrad_layer(hipStream_t s, int dim, const CnnGeom& g, const ConvIn& act, const ConvIn& dz,
+                 float* part, float* flat) {
+  if (dim == 2) wgrad_dim<2>(s, g, act, dz, part, flat);
+  else wgrad_dim<3>(s, g, act, dz, part, flat);
+}
+
+}  // namespace gkb

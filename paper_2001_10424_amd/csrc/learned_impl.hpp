@@ -52,21 +52,22 @@ __global__ __launch_bounds__(256) void k_pack_faces(Grid G, const T* __restrict_
   const long nc = G.n_cells;
   for (long c = (long)blockIdx.x * 256 + threadIdx.x; c < nc; c += (long)gridDim.x * 256) {
     const int i = int(c % G.n[0]), j = int((c / G.n[0]) % G.n[1]), k = int(c / ((long)G.n[0] * G.n[1]));
-    uint16_t* a = act + c * kCP;
+    constexpr int CG = 4;  // chan_group(DIM + 1)
+    uint16_t* a = act + c * CG;
     a[0] = f2bf(float(r[fidx<0>(G, i, j, k)]) * inv);
     a[1] = f2bf(float(r[fidx<1>(G, i, j, k)]) * inv);
     int ch = 2;
     if (DIM == 3) a[ch++] = f2bf(float(r[fidx<2>(G, i, j, k)]) * inv);
     a[ch++] = f2bf(logmu[c]);
-    for (; ch < kCP; ++ch) a[ch] = 0;
+    for (; ch < CG; ++ch) a[ch] = 0;
   }
 }
 
-// correction c = (s / lambda) y16[cell][component] on unknown faces that are
+// correction c = (s / lambda) y[cell][component] on unknown faces that are
 // the lower face of a cell, 0 elsewhere; partial c.rt
 template <typename T, int DIM, int C>
 __device__ __forceinline__ void unpack_face(const Grid& G, int idx, int k,
-                                            const float* __restrict__ y16, float scale,
+                                            const float* __restrict__ y, float scale,
                                             const T* __restrict__ rt, T* __restrict__ cv,
                                             double& a) {
   const int e0 = G.ext[C][0], e1 = G.ext[C][1];
@@ -75,13 +76,13 @@ __device__ __forceinline__ void unpack_face(const Grid& G, int idx, int k,
   const int f = fidx<C>(G, i, j, k);
   const int ic = C == 0 ? i : (C == 1 ? j : k);
   T v = T(0);
-  if (unk<C>(G, ic) && ic < G.n[C]) v = T(scale * y16[(long)cidx(G, i, j, k) * kCP + C]);
+  if (unk<C>(G, ic) && ic < G.n[C]) v = T(scale * y[(long)cidx(G, i, j, k) * DIM + C]);
   cv[f] = v;
   a += double(v) * double(rt[f]);
 }
 
 template <typename T, int DIM>
-__global__ __launch_bounds__(256) void k_unpack_c(Grid G, const float* __restrict__ y16,
+__global__ __launch_bounds__(256) void k_unpack_c(Grid G, const float* __restrict__ y,
                                                   const PcgState* __restrict__ st, double mu_n,
                                                   double lam, const T* __restrict__ rt,
                                                   T* __restrict__ cv, double* __restrict__ p_crt) {
@@ -90,9 +91,9 @@ __global__ __launch_bounds__(256) void k_unpack_c(Grid G, const float* __restric
   const int c = blockIdx.z / G.nze, k = blockIdx.z - c * G.nze;
   const int idx = blockIdx.x * 256 + threadIdx.x;
   double a = 0.0;
-  if (c == 0) unpack_face<T, DIM, 0>(G, idx, k, y16, scale, rt, cv, a);
-  else if (c == 1) unpack_face<T, DIM, 1>(G, idx, k, y16, scale, rt, cv, a);
-  else if (DIM == 3) unpack_face<T, DIM, 2>(G, idx, k, y16, scale, rt, cv, a);
+  if (c == 0) unpack_face<T, DIM, 0>(G, idx, k, y, scale, rt, cv, a);
+  else if (c == 1) unpack_face<T, DIM, 1>(G, idx, k, y, scale, rt, cv, a);
+  else if (DIM == 3) unpack_face<T, DIM, 2>(G, idx, k, y, scale, rt, cv, a);
   __shared__ double sh[4];
   double t = block_sum<256>(a, sh);
   if (threadIdx.x == 0) p_crt[blockIdx.z * gridDim.x + blockIdx.x] = t;
@@ -345,33 +346,15 @@ void learned_apply(gkb_ctx* c, Inner<T>& in, const T* r_in, T* z_out, const PcgS
   else
     k_pack_faces<T, 3><<<nb, 256, 0, s>>>(G, rt, st, double(L->m_unknown), L->logmu, net->act[0]);
   CnnGeom g{G.n[0], G.n[1], G.n[2], 1, (long)G.n_cells};
-  const int blocks = conv_blocks(g.P);
-  const int* f1 = &st->done;
-  const int* f2 = &st->fallback;
-  for (int l = 0; l < net->L; ++l) {
-    const uint16_t* w = net->wf + (size_t)l * net->taps * 256;
-    const float* b = net->bias + 16 * l;
-    const int cin = net->ch[l];
-    if (G.dim == 2) {
-      if (l < net->L - 1)
-        launch_conv<2, kOutReluBf16>(cin, blocks, s, g, net->act[l], w, b, net->act[l + 1], nullptr, f1, f2);
-      else
-        launch_conv<2, kOutF32>(cin, blocks, s, g, net->act[l], w, b, net->y16, nullptr, f1, f2);
-    } else {
-      if (l < net->L - 1)
-        launch_conv<3, kOutReluBf16>(cin, blocks, s, g, net->act[l], w, b, net->act[l + 1], nullptr, f1, f2);
-      else
-        launch_conv<3, kOutF32>(cin, blocks, s, g, net->act[l], w, b, net->y16, nullptr, f1, f2);
-    }
-  }
+  cnn_layers(s, net, g, cnn_act0(net), net->y, &st->done, &st->fallback);
   // c (stored in z_out) with c.rt, then M c (into the rt buffer) with c.Mc,
   // the energy-optimal weight theta, and z = zv + theta c
   const dim3 tg = transfer_grid(G);
   if (G.dim == 2)
-    k_unpack_c<T, 2><<<tg, 256, 0, s>>>(G, net->y16, st, double(L->m_unknown), L->lam, rt,
+    k_unpack_c<T, 2><<<tg, 256, 0, s>>>(G, net->y, st, double(L->m_unknown), L->lam, rt,
                                         z_out, c->part[3]);
   else
-    k_unpack_c<T, 3><<<tg, 256, 0, s>>>(G, net->y16, st, double(L->m_unknown), L->lam, rt,
+    k_unpack_c<T, 3><<<tg, 256, 0, s>>>(G, net->y, st, double(L->m_unknown), L->lam, rt,
                                         z_out, c->part[3]);
   face_op<T, kApplyDot>(c, L0.op, L0.fl, z_out, nullptr, rt, T(0), c->part[4], st_dot);
   k_set_theta<<<1, kFinal, 0, s>>>(st, c->part[3], (int)(tg.x * tg.z), c->part[4],
