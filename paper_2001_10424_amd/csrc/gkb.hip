@@ -282,14 +282,14 @@ void csr_face_op(gkb_ctx* c, T eta, const T* x, const T* b, T* y, double* partia
   if constexpr (MODE == kApply || MODE == kApplyDot || MODE == kResid || MODE == kResidDot ||
                 MODE == kDiag) {
     T* t = csr_tmp<T>(c);
-    if (MODE != kDiag && eta != T(0)) k_csr_at<T><<<vec_blocks(o.n), kBlock, 0, s>>>(o, x, t, st);
-    k_csr_m<T, MODE><<<vec_blocks(o.m), kBlock, 0, s>>>(o, eta, x, t, b, y, partial, st);
+    if (MODE != kDiag && eta != T(0)) k_csr_at<T><<<csr_blocks(o.n), kBlock, 0, s>>>(o, x, t, st);
+    k_csr_m<T, MODE><<<csr_blocks(o.m), kBlock, 0, s>>>(o, eta, x, t, b, y, partial, st);
   }
 }
 
 // partials written by the A^T kernel (div_axpy)
 int div_parts(const gkb_ctx* c) {
-  return c->csr ? vec_blocks(c->g.n_cells) : cell_parts(c->g);
+  return c->csr ? csr_blocks(c->g.n_cells) : cell_parts(c->g);
 }
 
 // ec / Gc: coarse correction and coarse grid of kJacobiP (unused otherwise)
@@ -336,7 +336,7 @@ void face_op(gkb_ctx* c, const Op<T>& op, const FaceLaunch& fl, const T* x, cons
 
 void grad_axpy(gkb_ctx* c, const double* q, const double* yv, double s1, double s2, double* out) {
   if (c->csr) {
-    k_csr_grad<<<vec_blocks(c->g.m_full), kBlock, 0, c->cs>>>(c->csr64, q, yv, s1, s2, out);
+    k_csr_grad<<<csr_blocks(c->g.m_full), kBlock, 0, c->cs>>>(c->csr64, q, yv, s1, s2, out);
     return;
   }
   const FaceLaunch& fl = c->fl0;
@@ -350,7 +350,7 @@ template <typename T>
 void div_axpy(gkb_ctx* c, const Grid& g, const T* x, const T* z, double s1, double s2, T* t,
               double* partial, double* zz) {
   if (c->csr) {
-    k_csr_div<T><<<vec_blocks(g.n_cells), kBlock, 0, c->cs>>>(csr_of<T>(c), x, z, s1, s2, t,
+    k_csr_div<T><<<csr_blocks(g.n_cells), kBlock, 0, c->cs>>>(csr_of<T>(c), x, z, s1, s2, t,
                                                                partial, zz);
     return;
   }
@@ -653,41 +653,67 @@ int ensure_graph(gkb_ctx* c, Inner<T>& in, int count) {
 // x += Z y, and the next cycle's start from the true residual r = f - M x
 // (f in in.rprev).  Every kernel skips once its flag is set, so the launch
 // sequence is fixed and is captured as one graph.
+template <typename T, int Q>
+void fgmres_orthogonalise(gkb_ctx* c, Inner<T>& in, int nv, const T* z, T* w) {
+  const int n = in.lv[0].g.m_full, gb = gm_blocks(n);
+  const bool fold = gm_folded(n);
+  const long ld = n;
+  hipStream_t s = c->cs;
+  double* const part[2] = {in.gm_part, in.gm_part + (fold ? (size_t)nv * gb : 0)};
+  // partials of nv sums as the next kernel takes them
+  auto ready = [&](double* p, int count) -> double* {
+    if (fold) return p;
+    k_gm_sums<<<count, kFinal, 0, s>>>(in.gm_cyc, in.gm_fs, p, gb);
+    return in.gm_fs->sum;
+  };
+  const int nb = fold ? gb : 1;
+  if (z)
+    k_gm_csr_dots<T, Q><<<gb, kBlock, 0, s>>>(csr_of<T>(c), in.lv[0].op.eta, in.gm_cyc, z,
+                                              csr_tmp<T>(c), in.gm_V, ld, nv, w, part[0]);
+  else
+    k_gm_dots<T, Q><<<gb, kBlock, 0, s>>>(n, in.gm_cyc, in.gm_V, ld, nv, w, part[0]);
+  double* p0 = ready(part[0], nv);
+  k_gm_pass<T, Q, 0><<<gb, kBlock, 0, s>>>(n, in.gm_cyc, in.gm_fs, in.gm_V, ld, nv, p0, nb, w, w,
+                                           part[1]);
+  double* p1 = ready(part[1], nv);
+  k_gm_pass<T, Q, 1><<<gb, kBlock, 0, s>>>(n, in.gm_cyc, in.gm_fs, in.gm_V, ld, nv, p1, nb, w,
+                                           in.q, part[0]);
+  ready(part[0], 1);
+}
+
 template <typename T>
 void fgmres_cycle(gkb_ctx* c, Inner<T>& in) {
   const Level<T>& L0 = in.lv[0];
-  const int n = L0.g.m_full, vb = vec_blocks(n);
+  const int n = L0.g.m_full, gb = gm_blocks(n), nb = gm_folded(n) ? gb : 1;
   const int R = c->opt.fgmres_restart;
   const long ld = n;
   hipStream_t s = c->cs;
   const bool jac = c->opt.inner == GKB_INNER_JACOBI;
   const bool learned = c->opt.inner == GKB_INNER_LEARNED && learned_has_net(c->learned);
+  const double* pww = gm_folded(n) ? in.gm_part : in.gm_fs->sum;  // partials of w.w
+  const bool at = jac && c->csr && L0.op.eta != T(0);
   for (int j = 0; j < R; ++j) {
     T* vj = in.gm_V + j * ld;
     T* zj = in.gm_Z + j * ld;
     T* w = in.gm_V + (j + 1) * ld;
-    if (jac) k_gm_jacobi<T><<<vb, kBlock, 0, s>>>(n, in.gm_cyc, in.dinv, vj, zj);
-    else if (learned) learned_apply<T>(c, in, vj, zj, in.gm_cyc, in.gm_cyc);
-    else vcycle<T>(c, in, 0, vj, zj, nullptr, in.gm_cyc);
-    face_op<T, kApply>(c, L0.op, L0.fl, zj, nullptr, w, T(0), nullptr, in.gm_cyc);
+    k_gm_next<T><<<gb, kBlock, 0, s>>>(n, in.st, in.gm_cyc, in.gm_fs, pww, nb, j,
+                                       j == 0 ? in.r : in.q, vj, jac ? in.dinv : nullptr, zj,
+                                       csr_of<T>(c), at ? csr_tmp<T>(c) : nullptr);
+    if (learned) learned_apply<T>(c, in, vj, zj, in.gm_cyc, in.gm_cyc);
+    else if (!jac) vcycle<T>(c, in, 0, vj, zj, nullptr, in.gm_cyc);
+    const T* zc = c->csr ? zj : nullptr;
+    if (!zc) face_op<T, kApply>(c, L0.op, L0.fl, zj, nullptr, w, T(0), nullptr, in.gm_cyc);
     const int nv = j + 1;
-    const dim3 dg(vb, (nv + kGmChunk - 1) / kGmChunk);
-    for (int pass = 0; pass < 2; ++pass) {
-      k_gm_mdot<T><<<dg, kBlock, 0, s>>>(n, in.gm_cyc, in.gm_V, ld, nv, w, in.gm_part);
-      k_gm_hsum<<<1, kFinal, 0, s>>>(in.gm_cyc, in.gm_fs, in.gm_part, vb, nv, j, pass);
-      k_gm_maxpy<T><<<vb, kBlock, 0, s>>>(n, in.gm_cyc, in.gm_fs, in.gm_V, ld, nv, w, c->part[0]);
-    }
-    k_gm_arnoldi_end<<<1, kFinal, 0, s>>>(in.st, in.gm_cyc, in.gm_fs, c->part[0], vb, j,
-                                          j == R - 1 ? 1 : 0);
-    k_gm_scale<T><<<vb, kBlock, 0, s>>>(n, in.gm_cyc, in.gm_fs, j, w);
+    if (nv <= 8) fgmres_orthogonalise<T, 8>(c, in, nv, zc, w);
+    else if (nv <= 16) fgmres_orthogonalise<T, 16>(c, in, nv, zc, w);
+    else if (nv <= 32) fgmres_orthogonalise<T, 32>(c, in, nv, zc, w);
+    else fgmres_orthogonalise<T, 64>(c, in, nv, zc, w);
   }
-  k_gm_solve_y<<<1, 64, 0, s>>>(in.st, in.gm_fs);
-  k_gm_update_x<T><<<vb, kBlock, 0, s>>>(n, in.st, in.gm_fs, in.gm_Z, ld, in.x);
-  k_gm_cycle_end<<<1, 64, 0, s>>>(in.st, in.gm_fs);
+  k_gm_finish<<<1, kBlock, 0, s>>>(in.st, in.gm_cyc, in.gm_fs, pww, nb, R);
+  k_gm_update_x<T><<<gb, kBlock, 0, s>>>(n, in.st, in.gm_fs, in.gm_Z, ld, in.x);
   face_op<T, kResidDot>(c, L0.op, L0.fl, in.x, in.rprev, in.r, T(0), c->part[1], in.st);
   k_gm_start<<<1, kFinal, 0, s>>>(in.st, in.gm_cyc, in.gm_fs, c->part[1], L0.fl.nparts, 0.0, 0, 0,
                                   sizeof(T) == 4 ? 1 : 0);
-  k_gm_v0<T><<<vb, kBlock, 0, s>>>(n, in.st, in.gm_fs, in.r, in.gm_V);
 }
 
 int learned_prepare(gkb_ctx* c);
@@ -710,7 +736,6 @@ int fgmres_solve(gkb_ctx* c, const double* f, double* x_out, double tol, int* it
   k_cast<T, T><<<vb, kBlock, 0, s>>>(n, in.r, in.rprev);  // f in working precision
   k_gm_start<<<1, kFinal, 0, s>>>(in.st, in.gm_cyc, in.gm_fs, c->part[3], vb, tol,
                                   c->opt.inner_maxit, 1, 0);
-  k_gm_v0<T><<<vb, kBlock, 0, s>>>(n, in.st, in.gm_fs, in.r, in.gm_V);
   if (c->opt.use_graphs && !in.graph_gm) {
     hipGraph_t gr;
     HIPCK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
@@ -972,8 +997,8 @@ int residual_impl(gkb_ctx* c, const double* gv, const double* rv, const double* 
   if (c->csr) {
     CsrOps<double> o = c->csr64;
     if (user_space) o.sw = o.sp = nullptr;
-    nw = vec_blocks(o.m);
-    nr = vec_blocks(o.n);
+    nw = csr_blocks(o.m);
+    nr = csr_blocks(o.n);
     k_csr_resid_w<<<nw, kBlock, 0, s>>>(o, gv, w, p, res_w, c->part[0], c->part[1]);
     k_csr_div<double><<<nr, kBlock, 0, s>>>(o, w, rv, -1.0, 1.0, res_r ? res_r : c->t, c->part[2],
                                             c->part[3]);
@@ -1321,7 +1346,7 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
     lv.omega = c->omega[l];
     if (c->csr) {
       lv.fl = FaceLaunch{};
-      lv.fl.nparts = lv.fl.gparts = vec_blocks(lv.g.m_full);
+      lv.fl.nparts = lv.fl.gparts = csr_blocks(lv.g.m_full);
     } else {
       lv.fl = face_launch(lv.g, 4, c->opt.stencil);
       if (l < L - 1) lv.leg = level_legs(c, lv.g, sizeof(T));
@@ -1363,7 +1388,7 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
     CK(c->mem.arr(&in.gm_Z, (size_t)R * m));
     CK(c->mem.arr(&in.gm_fs, 1));
     CK(c->mem.arr(&in.gm_cyc, 1));
-    CK(c->mem.arr(&in.gm_part, (size_t)(R + 1) * vec_blocks(m)));
+    CK(c->mem.arr(&in.gm_part, (size_t)(R + 1) * gm_blocks(m) * (gm_folded(m) ? 2 : 1)));
   }
   // Jacobi preconditioner 1/diag(M) (0 at non-unknown faces)
   CK(c->mem.arr(&in.dinv, m));
@@ -1721,8 +1746,8 @@ int setup_csr_impl(gkb_ctx* c, const gkb_csr* sys, double eta, int scaling, cons
   c->op32.g = G;
   c->op32.eta = float(eta);
   c->fl0 = FaceLaunch{};
-  c->fl0.nparts = c->fl0.gparts = vec_blocks(m);
-  c->maxparts = std::max(vec_blocks(m), vec_blocks(n));
+  c->fl0.nparts = c->fl0.gparts = csr_blocks(m);
+  c->maxparts = std::max(csr_blocks(m), csr_blocks(n));
   for (int i = 0; i < kSlots; ++i) CK(c->mem.arr(&c->part[i], c->maxparts));
   CK(c->mem.arr(&c->dscal, 8));
   HIPCK(hipHostMalloc(reinterpret_cast<void**>(&c->hbuf), 4096, hipHostMallocDefault));
