@@ -238,7 +238,6 @@ struct gkb_ctx {
   double *b = nullptr, *q = nullptr, *d = nullptr, *t = nullptr, *rr = nullptr, *dp = nullptr;
   double* part[kSlots] = {nullptr};
   int maxparts = 0;
-  double* dscal = nullptr;
   double* hbuf = nullptr;  // pinned host
   FaceLaunch fl0;
   gkb_stats_t stats;
@@ -360,9 +359,21 @@ void div_axpy(gkb_ctx* c, const Grid& g, const T* x, const T* z, double s1, doub
     k_div_axpy<T, 3><<<cell_grid(g), kBlock, 0, c->cs>>>(g, x, z, s1, s2, t, partial, zz);
 }
 
+void launch_saddle(const Op<double>& op, bool varmu, const double* g, const double* r,
+                   const double* w, const double* p, double* res_w, double* res_r, double* p_rr,
+                   double* p_gg, double* p_tt, double* p_zz, hipStream_t s) {
+  const SaddleLaunch L = saddle_launch(op.g);
+  auto go = [&](auto kernel) {
+    kernel<<<L.blocks, kSaddleBlock, 0, s>>>(op, g, r, w, p, res_w, res_r, L.kz, L.bx, p_rr, p_gg,
+                                             p_tt, p_zz);
+  };
+  if (op.g.dim == 2) varmu ? go(k_saddle<2, true>) : go(k_saddle<2, false>);
+  else varmu ? go(k_saddle<3, true>) : go(k_saddle<3, false>);
+}
+
 int host_sum(gkb_ctx* c, const double* partial, int n, double* out) {
-  k_sum_partials<<<1, kFinal, 0, c->cs>>>(partial, n, c->dscal);
-  HIPCK(hipMemcpyAsync(c->hbuf, c->dscal, sizeof(double), hipMemcpyDeviceToHost, c->cs));
+  // into the pinned buffer by the kernel's own store, without a copy
+  k_sum_partials<<<1, kFinal, 0, c->cs>>>(partial, n, c->hbuf);
   HIPCK(hipStreamSynchronize(c->cs));
   *out = c->hbuf[0];
   return GKB_OK;
@@ -1003,26 +1014,14 @@ int residual_impl(gkb_ctx* c, const double* gv, const double* rv, const double* 
     k_csr_div<double><<<nr, kBlock, 0, s>>>(o, w, rv, -1.0, 1.0, res_r ? res_r : c->t, c->part[2],
                                             c->part[3]);
   } else {
-    Op<double> opW = c->op64;
-    opW.eta = 0.0;
-    const FaceLaunch& fl = c->fl0;
-    const bool vm = opW.mu != nullptr;
-    if (G.dim == 2) {
-      if (vm) k_resid_w<2, true><<<fl.grid, kBlock, 0, s>>>(opW, gv, w, p, res_w, fl.kz, fl.zchunks, c->part[0], c->part[1]);
-      else k_resid_w<2, false><<<fl.grid, kBlock, 0, s>>>(opW, gv, w, p, res_w, fl.kz, fl.zchunks, c->part[0], c->part[1]);
-    } else {
-      if (vm) k_resid_w<3, true><<<fl.grid, kBlock, 0, s>>>(opW, gv, w, p, res_w, fl.kz, fl.zchunks, c->part[0], c->part[1]);
-      else k_resid_w<3, false><<<fl.grid, kBlock, 0, s>>>(opW, gv, w, p, res_w, fl.kz, fl.zchunks, c->part[0], c->part[1]);
-    }
-    div_axpy<double>(c, G, w, rv, -1.0, 1.0, res_r ? res_r : c->t, c->part[2], c->part[3]);
-    nw = fl.gparts;
-    nr = cell_parts(G);
+    launch_saddle(c->op64, c->varmu, gv, rv, w, p, res_w, res_r ? res_r : c->t, c->part[0],
+                  c->part[1], c->part[2], c->part[3], s);
+    nw = nr = saddle_launch(G).blocks;
   }
-  double rw = 0, ggw = 0, rrr = 0, rr2 = 0;
-  CK(host_sum(c, c->part[0], nw, &rw));
-  CK(host_sum(c, c->part[1], nw, &ggw));
-  CK(host_sum(c, c->part[2], nr, &rrr));
-  CK(host_sum(c, c->part[3], nr, &rr2));
+  // the sums go to the pinned buffer by the kernel's own stores
+  k_sum_four<<<4, kFinal, 0, s>>>(c->part[0], c->part[1], c->part[2], c->part[3], nw, nr, c->hbuf);
+  HIPCK(hipStreamSynchronize(s));
+  const double rw = c->hbuf[0], ggw = c->hbuf[1], rrr = c->hbuf[2], rr2 = c->hbuf[3];
   norms[0] = std::sqrt(rw + rrr);
   norms[1] = std::sqrt(rw);
   norms[2] = std::sqrt(rrr);
@@ -1519,7 +1518,6 @@ int setup_impl(gkb_ctx* c, const gkb_grid* grid, const double* visc, double eta,
   }
   c->maxparts = maxp;
   for (int i = 0; i < kSlots; ++i) CK(c->mem.arr(&c->part[i], maxp));
-  CK(c->mem.arr(&c->dscal, 8));
   HIPCK(hipHostMalloc(reinterpret_cast<void**>(&c->hbuf), 4096, hipHostMallocDefault));
   const int m = c->g.m_full, nc = c->g.n_cells;
   double** fv[] = {&c->ghat, &c->w0, &c->u, &c->v, &c->Mv, &c->s, &c->y, &c->f, &c->rw, &c->dw};
@@ -1749,7 +1747,6 @@ int setup_csr_impl(gkb_ctx* c, const gkb_csr* sys, double eta, int scaling, cons
   c->fl0.nparts = c->fl0.gparts = csr_blocks(m);
   c->maxparts = std::max(csr_blocks(m), csr_blocks(n));
   for (int i = 0; i < kSlots; ++i) CK(c->mem.arr(&c->part[i], c->maxparts));
-  CK(c->mem.arr(&c->dscal, 8));
   HIPCK(hipHostMalloc(reinterpret_cast<void**>(&c->hbuf), 4096, hipHostMallocDefault));
   double** fv[] = {&c->ghat, &c->w0, &c->u, &c->v, &c->Mv, &c->s, &c->y, &c->f, &c->rw, &c->dw};
   for (auto pp : fv) CK(c->mem.arr(pp, m));

@@ -178,54 +178,230 @@ __global__ __launch_bounds__(kBlock) void k_div_axpy(Grid G, const T* __restrict
   }
 }
 
-// FP64 velocity residual res = g - W w - A p on unknown faces; partials of
-// res.res and g.g (unknown faces)
-template <int DIM, bool VARMU, int C>
-__device__ __forceinline__ void resid_face(const Op<double>& op, const double* __restrict__ g,
-                                           const double* __restrict__ w,
-                                           const double* __restrict__ p, double* __restrict__ res,
-                                           int idx, int k0, int kz, double& rr, double& gg) {
+// ------------------------------------------------------ saddle residual
+
+// one neighbour of the viscous stencil: inside the array kap (xf - xn), across
+// a wall the mirror ghost 2 kap xf, else (do-nothing side) 0
+__device__ __forceinline__ double visc_side(bool in, bool wall, double kap, double xf, double xn) {
+  return in ? kap * (xf - xn) : (wall ? 2.0 * kap * xf : 0.0);
+}
+
+constexpr int kSaddleBlock = 512;
+
+// FP64 saddle residual in one pass: res_w = g - W w - A p on the unknown faces
+// (0 elsewhere, may be null), res_r = r - A^T w on the cells (0 at the pin);
+// partials of res_w.res_w, g.g (unknown faces), res_r.res_r, r.r (unpinned
+// cells) to part[0 .. 3][block].
+//
+// Bound by memory: at least g, w, p, r read and both results written.  A
+// thread owns the column (i, j) of lower faces and cells and marches kz planes
+// up, the plane below and the next one in registers; a block is a run of the
+// flattened (nx + 1) x (ny + 1) plane, so every extent fills its waves, and
+// blocks of one XCD are neighbours (rows and planes they share stay in its
+// L2).  Every load is unconditional from a clamped address, so a plane's loads
+// are in flight together.  128^3: 52 us (203 MB); one kernel per component
+// with branches around its loads and one for the cells took 64.5 + 18.7 us.
+template <int DIM, bool VARMU>
+__global__ __launch_bounds__(kSaddleBlock) void k_saddle(Op<double> op,
+                                                         const double* __restrict__ g,
+                                                         const double* __restrict__ r,
+                                                         const double* __restrict__ w,
+                                                         const double* __restrict__ p,
+                                                         double* __restrict__ res_w,
+                                                         double* __restrict__ res_r, int kz, int bx,
+                                                         double* __restrict__ p_rr,
+                                                         double* __restrict__ p_gg,
+                                                         double* __restrict__ p_tt,
+                                                         double* __restrict__ p_zz) {
   const Grid& G = op.g;
-  const int e0 = G.ext[C][0], e1 = G.ext[C][1], e2 = G.ext[C][2];
-  if (idx >= e0 * e1) return;
-  const int j = idx / e0, i = idx - j * e0;
-  for (int k = k0; k < k0 + kz && k < e2; ++k) {
-    const int ic = C == 0 ? i : (C == 1 ? j : k);
-    const int f = fidx<C>(G, i, j, k);
-    if (!unk<C>(G, ic)) {
-      if (res) res[f] = 0.0;
-      continue;
+  const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
+  const int nb = gridDim.x, xcd = blockIdx.x & 7;
+  const int lin = xcd * (nb >> 3) + min(xcd, nb & 7) + int(blockIdx.x >> 3);
+  const int k0 = (lin / bx) * kz;
+  const int e = (lin % bx) * kSaddleBlock + threadIdx.x;
+  const int j = e / (nx + 1), i = e - j * (nx + 1);
+  const bool col = j <= ny;
+  const bool cx = col && i < nx, cy = col && j < ny;  // a cell along x, along y
+  auto normal = [&](int c, int q) {  // faces at index q along their normal are unknowns
+    return q >= (G.bc[2 * c] == kDir ? 1 : 0) && q <= G.n[c] - (G.bc[2 * c + 1] == kDir ? 1 : 0);
+  };
+  const bool ux = normal(0, i), vy = normal(1, j);
+  const bool lx = G.bc[0] == kDir, hx = G.bc[1] == kDir, ly = G.bc[2] == kDir, hy = G.bc[3] == kDir,
+             lz = G.bc[4] == kDir, hz = G.bc[5] == kDir;
+  // w at a face, 0 where it is no unknown of the array
+  auto fu = [&](bool in, int ii, int jj, int kk) {
+    const double v = w[in ? fidx<0>(G, ii, jj, kk) : 0];
+    return in ? v : 0.0;
+  };
+  auto fv = [&](bool in, int ii, int jj, int kk) {
+    const double v = w[in ? fidx<1>(G, ii, jj, kk) : 0];
+    return in ? v : 0.0;
+  };
+  auto fw = [&](bool in, int ii, int jj, int kk) {
+    const double v = w[in ? fidx<2>(G, ii, jj, kk) : 0];
+    return in ? v : 0.0;
+  };
+  auto fp = [&](bool in, int ii, int jj, int kk) {
+    const int q = in ? cidx(G, ii, jj, kk) : 0;
+    const double v = p[q];
+    return in && q != G.pin ? v : 0.0;
+  };
+  const double gu = (i == 0 || i == nx) ? 0.5 : 1.0, gv = (j == 0 || j == ny) ? 0.5 : 1.0;
+  double rr = 0.0, gg = 0.0, tt = 0.0, zz = 0.0;
+  double uB = 0.0, vB = 0.0, wB = 0.0, pB = 0.0;
+  if (DIM == 3) {
+    const bool in = k0 > 0;
+    uB = fu(in && cy && ux, i, j, k0 - 1);
+    vB = fv(in && cx && vy, i, j, k0 - 1);
+    wB = fw(in && cx && cy && normal(2, k0 - 1), i, j, k0 - 1);
+    pB = fp(in && cx && cy, i, j, k0 - 1);
+  }
+  double uC = fu(cy && ux && k0 < nz, i, j, k0), vC = fv(cx && vy && k0 < nz, i, j, k0);
+  double wC = DIM == 3 ? fw(cx && cy && normal(2, k0), i, j, k0) : 0.0;
+  const int k1 = min(k0 + kz, DIM == 3 ? nz + 1 : 1);
+  for (int k = k0; k < k1; ++k) {
+    const bool cz = k < nz, cell = cx && cy && cz;
+    const bool onu = cy && cz && ux, onv = cx && cz && vy, onw = DIM == 3 && cx && cy && normal(2, k);
+    const int iu = onu ? fidx<0>(G, i, j, k) : 0, iv = onv ? fidx<1>(G, i, j, k) : 0,
+              iw = onw ? fidx<2>(G, i, j, k) : 0, ic = cell ? cidx(G, i, j, k) : 0;
+    // the face at i + 1 counts in the divergence also where i is a wall
+    const double uE = fu(cell && normal(0, i + 1), i + 1, j, k), uW = fu(onu && i > 0 && normal(0, i - 1), i - 1, j, k);
+    const double vN = fv(cell && normal(1, j + 1), i, j + 1, k), vS = fv(onv && j > 0 && normal(1, j - 1), i, j - 1, k);
+    const double uN = fu(onu && j < ny - 1, i, j + 1, k), uS = fu(onu && j > 0, i, j - 1, k);
+    const double vE = fv(onv && i < nx - 1, i + 1, j, k), vW = fv(onv && i > 0, i - 1, j, k);
+    const double pC = fp(cell, i, j, k), pW = fp(onu && i > 0, i - 1, j, k),
+                 pS = fp(onv && j > 0, i, j - 1, k);
+    const double gfu = g[iu], gfv = g[iv], rc = r[ic];
+    double uT = 0.0, vT = 0.0, wT = 0.0, wN = 0.0, wS = 0.0, wE = 0.0, wW = 0.0, gfw = 0.0;
+    if (DIM == 3) {
+      uT = fu(cy && ux && k < nz - 1, i, j, k + 1);
+      vT = fv(cx && vy && k < nz - 1, i, j, k + 1);
+      wT = fw(cell && normal(2, k + 1), i, j, k + 1);
+      wN = fw(onw && j < ny - 1, i, j + 1, k), wS = fw(onw && j > 0, i, j - 1, k);
+      wE = fw(onw && i < nx - 1, i + 1, j, k), wW = fw(onw && i > 0, i - 1, j, k);
+      gfw = g[iw];
     }
-    double mx, d;
-    stencil_M<double, DIM, VARMU, C>(op, w, i, j, k, mx, d);
-    const double gf = g[f];
-    const double v = gf - mx - grad_f<C>(G, p, i, j, k) * op.ih;
-    if (res) res[f] = v;
-    rr += v * v;
-    gg += gf * gf;
+    // viscosities: cells C, W, S, B and the edges around the three faces
+    double mC = 1.0, mW = 1.0, mS = 1.0, mB = 1.0, ez = 1.0, ezN = 1.0, ezE = 1.0, ey = 1.0,
+           eyT = 1.0, eyE = 1.0, ex = 1.0, exT = 1.0, exN = 1.0;
+    if (VARMU) {
+      const int a = min(i, nx - 1), b = min(j, ny - 1), c = min(k, nz - 1);
+      const int jv = min(j, ny);
+      mC = op.mu[cidx(G, a, b, c)];
+      mW = op.mu[cidx(G, max(i - 1, 0), b, c)];
+      mS = op.mu[cidx(G, a, min(max(j - 1, 0), ny - 1), c)];
+      ez = edge_mu<2>(op, i, jv, c), ezN = edge_mu<2>(op, i, min(j + 1, ny), c);
+      ezE = edge_mu<2>(op, min(i + 1, nx), jv, c);
+      if (DIM == 3) {
+        mB = op.mu[cidx(G, a, b, max(k - 1, 0))];
+        ey = edge_mu<1>(op, i, b, k), eyT = edge_mu<1>(op, i, b, min(k + 1, nz));
+        eyE = edge_mu<1>(op, min(i + 1, nx), b, k);
+        ex = edge_mu<0>(op, a, jv, k), exT = edge_mu<0>(op, a, jv, min(k + 1, nz));
+        exN = edge_mu<0>(op, a, min(j + 1, ny), k);
+      }
+    }
+    if (cy && cz) {
+      double v = 0.0;
+      if (ux) {
+        double m = 0.0, t = 0.0;
+        if (i > 0) m += mW * (uC - uW);
+        if (i < nx) m += mC * (uC - uE);
+        t += visc_side(j > 0, ly, ez, uC, uS);
+        t += visc_side(j < ny - 1, hy, ezN, uC, uN);
+        if (DIM == 3) {
+          t += visc_side(k > 0, lz, ey, uC, uB);
+          t += visc_side(k < nz - 1, hz, eyT, uC, uT);
+        }
+        v = gfu - (m + gu * t) * op.ih2 - (pC - pW) * op.ih;
+        rr += v * v;
+        gg += gfu * gfu;
+      }
+      if (res_w) res_w[fidx<0>(G, i, j, k)] = v;
+    }
+    if (cx && cz) {
+      double v = 0.0;
+      if (vy) {
+        double m = 0.0, t = 0.0;
+        if (j > 0) m += mS * (vC - vS);
+        if (j < ny) m += mC * (vC - vN);
+        t += visc_side(i > 0, lx, ez, vC, vW);
+        t += visc_side(i < nx - 1, hx, ezE, vC, vE);
+        if (DIM == 3) {
+          t += visc_side(k > 0, lz, ex, vC, vB);
+          t += visc_side(k < nz - 1, hz, exT, vC, vT);
+        }
+        v = gfv - (m + gv * t) * op.ih2 - (pC - pS) * op.ih;
+        rr += v * v;
+        gg += gfv * gfv;
+      }
+      if (res_w) res_w[fidx<1>(G, i, j, k)] = v;
+    }
+    if (DIM == 3 && cx && cy) {
+      double v = 0.0;
+      if (onw) {
+        const double gw = (k == 0 || k == nz) ? 0.5 : 1.0;
+        double m = 0.0, t = 0.0;
+        if (k > 0) m += mB * (wC - wB);
+        if (k < nz) m += mC * (wC - wT);
+        t += visc_side(i > 0, lx, ey, wC, wW);
+        t += visc_side(i < nx - 1, hx, eyE, wC, wE);
+        t += visc_side(j > 0, ly, ex, wC, wS);
+        t += visc_side(j < ny - 1, hy, exN, wC, wN);
+        v = gfw - (m + gw * t) * op.ih2 - (pC - pB) * op.ih;
+        rr += v * v;
+        gg += gfw * gfw;
+      }
+      if (res_w) res_w[fidx<2>(G, i, j, k)] = v;
+    }
+    if (cell) {
+      double v = 0.0;
+      if (ic != G.pin) {
+        double d = uC - uE;
+        d += vC - vN;
+        if (DIM == 3) d += wC - wT;
+        v = rc - d / G.h;
+        tt += v * v;
+        zz += rc * rc;
+      }
+      res_r[ic] = v;
+    }
+    uB = uC, vB = vC, wB = wC, pB = pC;
+    uC = uT, vC = vT, wC = wT;
+  }
+  __shared__ double sh[4][kSaddleBlock / 64];
+  const double v[4] = {wave_sum(rr), wave_sum(gg), wave_sum(tt), wave_sum(zz)};
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sh[q][threadIdx.x >> 6] = v[q];
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    double s = 0.0;
+    for (int q = 0; q < kSaddleBlock / 64; ++q) s += sh[threadIdx.x][q];
+    double* const out = threadIdx.x == 0 ? p_rr : threadIdx.x == 1 ? p_gg : threadIdx.x == 2 ? p_tt : p_zz;
+    out[blockIdx.x] = s;
   }
 }
 
-template <int DIM, bool VARMU>
-__global__ __launch_bounds__(kBlock) void k_resid_w(Op<double> op, const double* __restrict__ g,
-                                                    const double* __restrict__ w,
-                                                    const double* __restrict__ p,
-                                                    double* __restrict__ res, int kz, int zchunks,
-                                                    double* __restrict__ part_rr,
-                                                    double* __restrict__ part_gg) {
-  const int c = blockIdx.z / zchunks;
-  const int k0 = (blockIdx.z - c * zchunks) * kz;
-  const int idx = blockIdx.x * kBlock + threadIdx.x;
-  double rr = 0.0, gg = 0.0;
-  if (c == 0) resid_face<DIM, VARMU, 0>(op, g, w, p, res, idx, k0, kz, rr, gg);
-  else if (c == 1) resid_face<DIM, VARMU, 1>(op, g, w, p, res, idx, k0, kz, rr, gg);
-  else if (DIM == 3) resid_face<DIM, VARMU, 2>(op, g, w, p, res, idx, k0, kz, rr, gg);
-  __shared__ double sh[kBlock / 64];
-  double s = block_sum<kBlock>(rr, sh);
-  if (threadIdx.x == 0) part_rr[blockIdx.z * gridDim.x + blockIdx.x] = s;
-  __syncthreads();
-  s = block_sum<kBlock>(gg, sh);
-  if (threadIdx.x == 0) part_gg[blockIdx.z * gridDim.x + blockIdx.x] = s;
+// planes per thread and blocks of k_saddle: four planes amortise the columns'
+// first loads, two where that leaves fewer than about 1000 blocks of waves;
+// never more partials than the face kernels' launches have
+struct SaddleLaunch {
+  int kz, bx, blocks;
+};
+inline SaddleLaunch saddle_launch(const Grid& g) {
+  const int bx = ((g.n[0] + 1) * (g.n[1] + 1) + kSaddleBlock - 1) / kSaddleBlock;
+  const int kz = g.dim == 2 ? 1 : (bx * ((g.nze + 3) / 4) >= 1000 ? 4 : 2);
+  return {kz, bx, bx * ((g.nze + kz - 1) / kz)};
+}
+
+// sums of four partial arrays, one block each
+__global__ __launch_bounds__(kFinal) void k_sum_four(const double* a, const double* b,
+                                                     const double* c, const double* d, int n,
+                                                     int n2, double* out) {
+  __shared__ double sh[kFinal / 64];
+  const double* const src = blockIdx.x == 0 ? a : blockIdx.x == 1 ? b : blockIdx.x == 2 ? c : d;
+  const double s = sum_partials(src, blockIdx.x < 2 ? n : n2, sh);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // --------------------------------------------------------- vector kernels

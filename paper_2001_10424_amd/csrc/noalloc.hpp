@@ -47,11 +47,10 @@ extern "C" int gkb_residual_noalloc(const gkb_grid* grid, const double* g, const
   CK(validate(grid, 0.0, &o));
   const int n[3] = {grid->n[0], grid->n[1], grid->dim == 3 ? grid->n[2] : 1};
   const Grid G = make_grid(grid->dim, n, grid->h, grid->bc, grid->pin_cell);
-  // the generic face kernel's launch, the same as gkb_residual's, so both
-  // reduce in the same order
+  // the limit stands in partials of the generic face and cell launches (the
+  // residual kernel, the same as gkb_residual's, has fewer)
   const FaceLaunch fl = face_launch(G, 4, 1);
-  const int pw = fl.gparts, pc = cell_parts(G);
-  if (pw > kScratchParts || pc > kScratchParts) return GKB_EINVAL;  // grid too large
+  if (fl.gparts > kScratchParts || cell_parts(G) > kScratchParts) return GKB_EINVAL;  // too large
   double* sc = nullptr;
   CK(scratch_on_current_device(&sc));
   double *p_rr = sc, *p_gg = sc + kScratchParts, *p_tt = sc + 2 * kScratchParts,
@@ -62,20 +61,10 @@ extern "C" int gkb_residual_noalloc(const gkb_grid* grid, const double* g, const
   opW.eta = 0.0;
   opW.ih2 = 1.0 / (G.h * G.h);
   opW.ih = 1.0 / G.h;
-  if (G.dim == 2)
-    k_resid_w<2, false><<<fl.grid, kBlock, 0, s>>>(opW, g, w, p, res_w, fl.kz, fl.zchunks, p_rr, p_gg);
-  else
-    k_resid_w<3, false><<<fl.grid, kBlock, 0, s>>>(opW, g, w, p, res_w, fl.kz, fl.zchunks, p_rr, p_gg);
   // res_r = r - A^T w (required: the cell residual is formed in it)
-  double* t_out = res_r;
-  if (G.dim == 2)
-    k_div_axpy<double, 2><<<cell_grid(G), kBlock, 0, s>>>(G, w, r, -1.0, 1.0, t_out, p_tt, p_zz);
-  else
-    k_div_axpy<double, 3><<<cell_grid(G), kBlock, 0, s>>>(G, w, r, -1.0, 1.0, t_out, p_tt, p_zz);
-  k_sum_partials<<<1, kFinal, 0, s>>>(p_rr, pw, sums + 0);
-  k_sum_partials<<<1, kFinal, 0, s>>>(p_gg, pw, sums + 1);
-  k_sum_partials<<<1, kFinal, 0, s>>>(p_tt, pc, sums + 2);
-  k_sum_partials<<<1, kFinal, 0, s>>>(p_zz, pc, sums + 3);
+  launch_saddle(opW, false, g, r, w, p, res_w, res_r, p_rr, p_gg, p_tt, p_zz, s);
+  const int np = saddle_launch(G).blocks;
+  k_sum_four<<<4, kFinal, 0, s>>>(p_rr, p_gg, p_tt, p_zz, np, np, sums);
   HIPCK(hipGetLastError());
   double h[4];
   HIPCK(hipMemcpyAsync(h, sums, sizeof(h), hipMemcpyDeviceToHost, s));
