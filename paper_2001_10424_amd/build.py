@@ -21,7 +21,7 @@ FLAGS = [
 ]
 
 
-SOURCES = ("gkb.hip", "legs.hip", "conv.hip")
+SOURCES = ("gkb.hip", "legs.hip", "march.hip", "conv.hip")
 
 
 def sources():

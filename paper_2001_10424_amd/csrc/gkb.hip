@@ -407,7 +407,9 @@ __global__ __launch_bounds__(kBlock) void k_jacobi_first(int n, T omega, const T
 LegPlan level_legs(const gkb_ctx* c, const Grid& g, int elem) {
   const int nu = c->opt.smoother == GKB_SMOOTH_HYBRID ? 1 : 2;
   if (c->csr || c->opt.stencil != 0 || c->opt.nu_pre != nu || c->opt.nu_post != nu) return LegPlan();
-  return leg_plan(g, nu == 1, elem);
+  const LegPlan p = leg_plan(g, nu == 1, elem);
+  if (p.tile || nu == 1 || c->varmu) return p;
+  return march_plan(g, elem, c->smooth_transfer);
 }
 
 // first_done: the first pre-smoothing sweep from a zero guess is already in
@@ -434,9 +436,11 @@ void vcycle(gkb_ctx* c, Inner<T>& in, int l, const T* b, T* x, double* dot_parti
                           T(L.omega_e), c->smooth_transfer ? 1 : 0};
     // a coarse level that runs separate kernels finds its first sweep done
     T* x0c = (Lc.dinv && !Lc.leg.tile) ? ((tot - 1) % 2 == 0 ? Lc.x : Lc.t) : nullptr;
-    leg_down<T>(s, L.leg, leg, b, L.t, Lc.b, Lc.dinv, T(Lc.omega), x0c, st, check);
+    if (marches(L.leg)) march_down<T>(s, L.leg, leg, b, L.t, Lc.b, Lc.dinv, T(Lc.omega), x0c, st);
+    else leg_down<T>(s, L.leg, leg, b, L.t, Lc.b, Lc.dinv, T(Lc.omega), x0c, st, check);
     vcycle<T>(c, in, l + 1, Lc.b, Lc.x, nullptr, st, x0c != nullptr);
-    leg_up<T>(s, L.leg, leg, Lc.x, L.t, b, x, dot_partial, st);
+    if (marches(L.leg)) march_up<T>(s, L.leg, leg, Lc.x, L.t, b, x, dot_partial, st);
+    else leg_up<T>(s, L.leg, leg, Lc.x, L.t, b, x, dot_partial, st);
     return;
   }
   const bool hybrid = L.edinv != nullptr;
@@ -589,7 +593,7 @@ int pcg_iterations(gkb_ctx* c, Inner<T>& in, int count) {
   // launches: the direction update joins the product (alternating as above)
   // and the three scalar steps join the kernels that need them, 4 + legs
   // kernels instead of 7 + legs (common.hpp).
-  const LegPlan ap = L0.leg.tile ? apply_plan(L0.g) : LegPlan();
+  const LegPlan ap = L0.leg.tile && !marches(L0.leg) ? apply_plan(L0.g) : LegPlan();
   if (!jac && ap.tile && std::max(ap.nblocks, L0.leg.nblocks) <= kFoldParts && in.p2) {
     const int xb = fold_blocks(n);
     for (int it = 0; it < count; ++it) {
@@ -1376,7 +1380,7 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
   CK(c->mem.arr(&in.r, m));
   CK(c->mem.arr(&in.z, m));
   CK(c->mem.arr(&in.p, m));
-  if (((sizeof(T) == 4 && c->fl0.tiled) || in.lv[0].leg.tile) && c->opt.inner != GKB_INNER_JACOBI)
+  if (((sizeof(T) == 4 && c->fl0.tiled) || (in.lv[0].leg.tile && !marches(in.lv[0].leg))) && c->opt.inner != GKB_INNER_JACOBI)
     CK(c->mem.arr(&in.p2, m));
   CK(c->mem.arr(&in.q, m));
   CK(c->mem.arr(&in.rprev, m));

@@ -12,10 +12,17 @@ struct LegPlan {
   int tile = 0;
   dim3 grid;
   int nblocks = 0;  // partials of the dot product that the way up can form
+  int tz = 0;       // planes per block of the marching legs
 };
 
 // plan of a level: size of an element in bytes, hybrid or Jacobi smoother
 LegPlan leg_plan(const Grid& g, bool hybrid, int elem);
+
+// The marching legs (march.hip) of large 3D levels with the Jacobi smoother and
+// constant viscosity; they take no folded convergence test
+constexpr int kMarchWide = 16, kMarchSquare = 17;
+inline bool marches(const LegPlan& p) { return p.tile >= kMarchWide; }
+LegPlan march_plan(const Grid& g, int elem, bool smooth);
 
 // what both legs read of a level
 template <typename T>
@@ -56,5 +63,12 @@ void leg_down(hipStream_t s, const LegPlan& plan, const LegLevel<T>& L, const T*
 template <typename T>
 void leg_up(hipStream_t s, const LegPlan& plan, const LegLevel<T>& L, const T* ec, const T* xi,
             const T* b, T* xo, double* partial, const PcgState* st);
+
+template <typename T>
+void march_down(hipStream_t s, const LegPlan& plan, const LegLevel<T>& L, const T* b, T* xo, T* bc,
+                const T* dinv_c, T omega_c, T* x0c, const PcgState* st);
+template <typename T>
+void march_up(hipStream_t s, const LegPlan& plan, const LegLevel<T>& L, const T* ec, const T* xi,
+              const T* b, T* xo, double* partial, const PcgState* st);
 
 }  // namespace gkb

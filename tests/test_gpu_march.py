@@ -1,0 +1,52 @@
+"""The marching V-cycle legs of the large 3D levels against the separate
+generic kernels (stencil = 1): extents that end inside, at and just past the
+tiles (32 x 16 and 16 x 16) and the chunks of planes, every boundary type, the
+pinned cell at the edge of a tile and chunk, both transfers, both precisions.
+
+Tolerance: the same V-cycle in the same precision with sums in another order.
+A level's operators amplify a rounding by at most |M| / |D| <= 3 and a cycle
+chains fewer than 40 of them, so 1e3 eps of the precision bounds the relative
+difference."""
+import numpy as np
+import pytest
+
+import problems as P
+
+D, N = P.DIRICHLET, P.NATURAL
+pytestmark = pytest.mark.gpu
+
+WALLS = (D,) * 6
+GRIDS = {
+    "exact": P.Grid(3, (64, 64, 96), 1 / 64, WALLS, 0),
+    "ragged": P.Grid(3, (72, 40, 88), 1 / 40, WALLS, (31 * 40 + 15) * 72 + 32),
+    "thin": P.Grid(3, (136, 72, 40), 1 / 72, (D, D, D, D, D, N), -1),
+    "nat": P.Grid(3, (48, 72, 88), 1 / 72, (N, D, D, N, N, N), -1),
+    "nat_x": P.Grid(3, (80, 48, 72), 1 / 48, (D, N, N, D, D, D), (36 * 48 + 47) * 80 + 79),
+}
+
+
+@pytest.mark.parametrize("transfer,precision", [
+    ("smooth", "fp64"), ("smooth", "mixed"), ("div", "fp64")])
+@pytest.mark.parametrize("name", list(GRIDS))
+def test_marching_legs_match_separate_kernels(name, transfer, precision):
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] march", name, transfer, precision, flush=True)
+    g = GRIDS[name]
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    # entries at faces that are no unknown must not matter
+    r = torch.tensor(np.random.default_rng(11).standard_normal(g.m_full), dtype=dt, device="cuda")
+    out = []
+    for stencil in (0, 1):
+        s = gk.Solver(g, None, 1e2, inner="mg", stencil=stencil, nu_pre=2, nu_post=2,
+                      mg_transfer=transfer, precision=precision)
+        z = s.precondition(r, precision)
+        assert torch.equal(z, s.precondition(r, precision))
+        out.append(z.double().cpu().numpy())
+        s.close()
+    assert np.all(out[0][g.face_mask() == 0] == 0)
+    eps = 2.0 ** -52 if precision == "fp64" else 2.0 ** -23
+    err = np.linalg.norm(out[0] - out[1]) / np.linalg.norm(out[1])
+    big = np.abs(out[0] - out[1]).max() / np.abs(out[1]).max()
+    print("   relative difference", err, big, flush=True)
+    assert err <= 1e3 * eps and big <= 1e4 * eps
