@@ -15,6 +15,7 @@ namespace {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -29,6 +30,12 @@ struct CTile {
   static constexpr int TAPS = DIM == 3 ? 27 : 9;
 };
 
+// four values rounded to BF16 (to nearest even, the packed conversion of the
+// hardware)
+__device__ __forceinline__ s16x4 round4(f32x4 v) {
+  return __builtin_bit_cast(s16x4, __builtin_convertvector(v, bf16x4));
+}
+
 struct TileAt {
   int x, y, z;  // origin
   long base;    // first point of the batch entry
@@ -39,6 +46,20 @@ __host__ __device__ inline long tile_count(const CnnGeom& g) {
   typedef CTile<DIM> C;
   return (long)((g.nx + C::TX - 1) / C::TX) * ((g.ny + C::TY - 1) / C::TY) *
          ((g.nz + C::TZ - 1) / C::TZ) * g.batch;
+}
+
+// The tiles of this block: first, first + step, .. < end.  Blocks with the same
+// index mod 8 run on one XCD and get one range of consecutive tiles, so the
+// halos that neighbours share come from that XCD's L2.  The grid is a multiple
+// of 8 blocks.
+struct TileRange {
+  unsigned first, end, step;
+};
+__device__ __forceinline__ TileRange my_tiles(unsigned tiles) {
+  const unsigned xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const unsigned lo = unsigned((unsigned long)tiles * xcd / 8),
+                 hi = unsigned((unsigned long)tiles * (xcd + 1) / 8);
+  return {lo + j, hi, gridDim.x >> 3};
 }
 
 template <int DIM>
@@ -55,59 +76,142 @@ __device__ __forceinline__ TileAt tile_at(const CnnGeom& g, unsigned t) {
   return r;
 }
 
-// CG channels of point q (BF16), from BF16 or FP32 storage
+// CG channels of a point as loaded (BF16, or FP32 to be rounded): point q +
+// row + x (q and row uniform)
 template <int CG, bool F32>
-__device__ __forceinline__ void load_point(const void* p, int c, long q, uint16_t* v) {
-  if constexpr (!F32) {
-    const s16x4* a = reinterpret_cast<const s16x4*>(static_cast<const uint16_t*>(p) + q * CG);
+struct Raw {
+  s16x4 h[F32 ? 1 : CG / 4];
+  f32x4 f[F32 ? CG / 4 : 1];
+  __device__ __forceinline__ void load(const void* p, int c, long q, unsigned row, unsigned x) {
+    if constexpr (!F32) {
+      const s16x4* a = reinterpret_cast<const s16x4*>(static_cast<const uint16_t*>(p) + q * CG) +
+                       (size_t)x * (CG / 4) + (size_t)row * (CG / 4);
 #pragma unroll
-    for (int e = 0; e < CG / 4; ++e) *reinterpret_cast<s16x4*>(v + 4 * e) = a[e];
-  } else {
-    const float* a = static_cast<const float*>(p) + q * c;
-    if (CG == 4 && c == 4 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {  // uniform
-      const f32x4 x = *reinterpret_cast<const f32x4*>(a);
+      for (int e = 0; e < CG / 4; ++e) h[e] = a[e];
+    } else {
+      const float* a = static_cast<const float*>(p) + q * c;
+      if (CG == 4 && c == 4 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {  // uniform
+        f[0] = *(reinterpret_cast<const f32x4*>(a) + (size_t)x + (size_t)row);
+        return;
+      }
+      a += ((size_t)x + row) * c;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = f2bf(x[e]);
-      return;
+      for (int e = 0; e < CG; ++e) f[e / 4][e % 4] = e < c ? a[e] : 0.f;
     }
-#pragma unroll
-    for (int e = 0; e < CG; ++e) v[e] = e < c ? f2bf(a[e]) : uint16_t(0);
   }
-}
+  __device__ __forceinline__ s16x4 get(int e) const {
+    if constexpr (F32) return round4(f[e]);
+    else return h[e];
+  }
+};
 
-// stage the tile (with halo: HALO 1, without: 0) into sh[point][CG]
+// Staging of a tile (with halo: HALO 1, without: 0) into sh[point][CG]: fetch
+// issues a thread's loads, store writes them to LDS.  With the halo a wave
+// takes whole rows of 34 points, so row, bounds and base are uniform and a
+// lane's part of the address never changes; every load comes from inside the
+// array (clamped) and a thread's loads are in flight together.  (Points dealt
+// out to the threads one by one cost 50 vector instructions each for division,
+// bounds and addresses.)
+template <int DIM, int CG, bool F32, int HALO>
+struct Stage {
+  typedef CTile<DIM> C;
+  static constexpr int SX = C::TX + 2 * HALO, SY = C::TY + 2 * HALO,
+                       SZ = DIM == 3 ? C::TZ + 2 * HALO : 1;
+  static constexpr int RPW = HALO ? 1 : 2;  // rows per wave and turn
+  static constexpr int ROWS = SY * SZ, PER = (ROWS + 4 * RPW - 1) / (4 * RPW);
+  static_assert(RPW * SX <= 64, "rows of a wave");
+  Raw<CG, F32> r[PER];
+  unsigned long rows;  // with the halo: bit l: row l of the box is in the grid
+  unsigned in;         // the lane's x is; without: bit q: the point of turn q is
+  __device__ __forceinline__ static int wave() {
+    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  }
+  __device__ __forceinline__ void fetch(const CnnGeom& g, const TileAt& t, const void* p, int c) {
+    const int lane = threadIdx.x & 63;
+    const int lx = RPW == 1 ? lane : lane % SX, sub = RPW == 1 ? 0 : lane / SX;
+    const int x = t.x + lx - HALO;
+    const bool inx = lx < SX && unsigned(x) < unsigned(g.nx);
+    const int xc = std::min(std::max(x, 0), g.nx - 1);
+    // row `row` of the box: first point in the grid's array, and whether it
+    // lies in the grid
+    auto place = [&](int row, bool& on) {
+      const int y = t.y + (DIM == 3 ? row % SY : row) - HALO,
+                z = DIM == 3 ? t.z + row / SY - HALO : 0;
+      on = row < ROWS && unsigned(y) < unsigned(g.ny) && unsigned(z) < unsigned(g.nz);
+      const int yc = std::min(std::max(y, 0), g.ny - 1), zc = std::min(std::max(z, 0), g.nz - 1);
+      return unsigned((zc * g.ny + yc) * g.nx);
+    };
+    in = inx ? 1u : 0u;
+    if constexpr (RPW == 1) {
+      // lane l places row l, and the wave takes its rows from the lanes: the
+      // scalar unit, one instruction per cycle for the whole compute unit,
+      // bounded the kernels when every wave placed its rows there (600
+      // instructions per tile and wave: 30 us a layer at 128^3, 26 us like this)
+      static_assert(ROWS <= 64, "a row per lane");
+      bool on;
+      const unsigned at = place(lane, on);
+      rows = __ballot(on);
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        r[q].load(p, c, t.base, unsigned(__builtin_amdgcn_readlane(at, wave() + 4 * q)), xc);
+    } else {
+      in = 0;
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        bool on;
+        const unsigned at = place((wave() + 4 * q) * RPW + sub, on);
+        r[q].load(p, c, t.base, 0u, at + xc);
+        in |= (on && inx ? 1u : 0u) << q;
+      }
+    }
+  }
+  __device__ __forceinline__ void store(uint16_t* sh) const {
+    const int lane = threadIdx.x & 63;
+    const int lx = RPW == 1 ? lane : lane % SX, sub = RPW == 1 ? 0 : lane / SX;
+    uint16_t* const d = sh + ((wave() * RPW + sub) * SX + lx) * CG;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      if (lx < SX && (wave() + 4 * q) * RPW + sub < ROWS)
+#pragma unroll
+        for (int e = 0; e < CG / 4; ++e) {
+          const s16x4 v = r[q].get(e);
+          const bool on = RPW == 1 ? in && ((rows >> (wave() + 4 * q)) & 1u) : (in >> q) & 1u;
+          *reinterpret_cast<s16x4*>(d + 4 * q * RPW * SX * CG + 4 * e) = on ? v : s16x4{0, 0, 0, 0};
+        }
+    }
+  }
+};
 template <int DIM, int CG, bool F32, int HALO>
 __device__ __forceinline__ void stage(const CnnGeom& g, const TileAt& t, const void* p, int c,
                                       uint16_t* sh) {
-  typedef CTile<DIM> C;
-  constexpr int SX = C::TX + 2 * HALO, SY = C::TY + 2 * HALO, SZ = DIM == 3 ? C::TZ + 2 * HALO : 1;
-  constexpr int N = SX * SY * SZ, PER = (N + kThreads - 1) / kThreads;
-  struct __align__(8) V {
-    uint16_t v[CG];
-  } r[PER];
+  Stage<DIM, CG, F32, HALO> s;
+  s.fetch(g, t, p, c);
+  s.store(sh);
+}
+
+// output of four consecutive channels 4 c4 .. of point p (acc + bias)
+template <int OUT>
+__device__ __forceinline__ void put(f32x4 v, void* __restrict__ out, long p, int c4, int cout,
+                                    int cgo, const uint16_t* __restrict__ mask) {
+  if constexpr (OUT == kOutF32) {
+    float* o = static_cast<float*>(out) + p * cout + 4 * c4;
 #pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = threadIdx.x + q * kThreads;
-    const int row = e / SX, x = t.x + e - row * SX - HALO,
-              y = t.y + (DIM == 3 ? row % SY : row) - HALO,
-              z = DIM == 3 ? t.z + row / SY - HALO : 0;
-    const bool in = e < N && unsigned(x) < unsigned(g.nx) && unsigned(y) < unsigned(g.ny) &&
-                    unsigned(z) < unsigned(g.nz);
-    if (in) {
-      load_point<CG, F32>(p, c, t.base + ((long)z * g.ny + y) * g.nx + x, r[q].v);
+    for (int e = 0; e < 4; ++e)
+      if (4 * c4 + e < cout) o[e] = v[e];
+  } else if (4 * c4 < cgo) {
+    // padded channels have weights, bias and mask 0
+    s16x4 h;
+    if (OUT == kOutReluBf16) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+      h = round4(v);
     } else {
+      const s16x4 mk = *reinterpret_cast<const s16x4*>(mask + p * cgo + 4 * c4);
+      h = round4(v);
 #pragma unroll
-      for (int k = 0; k < CG; ++k) r[q].v[k] = 0;
+      for (int e = 0; e < 4; ++e) h[e] = mk[e] > 0 ? h[e] : short(0);  // sign bit: <= 0
     }
-  }
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = threadIdx.x + q * kThreads;
-    if (e < N)
-#pragma unroll
-      for (int k = 0; k < CG / 4; ++k)
-        *reinterpret_cast<s16x4*>(sh + e * CG + 4 * k) =
-            *reinterpret_cast<const s16x4*>(r[q].v + 4 * k);
+    *reinterpret_cast<s16x4*>(static_cast<uint16_t*>(out) + p * cgo + 4 * c4) = h;
   }
 }
 
@@ -124,10 +228,9 @@ __device__ __forceinline__ int tap_offset(int t) {
 // for the whole block; the B operand (columns = points) comes from LDS, 16
 // bytes per lane and MFMA; a lane ends up with four consecutive channels of
 // one point, an 8-byte store.
-// Bound: LDS reads of the B operand, 1 KB per MFMA, and the staging in front
-// of them.  128^3, 4 -> 8 -> 8 -> 3 channels: 34 + 31 + 29 us; 104 + 194 + 198
-// us with per-tap gathers on activations padded to 16 channels, plus 71 us of
-// conversions to and from that padding.
+// (More than 8 output channels; k_conv_pair takes the others.)  Bound: LDS reads
+// of the B operand, 1 KB per MFMA, and the staging in front of them; 512^2, 3
+// -> 16 -> 16 -> 16 -> 2 channels: 44 us a forward call.
 template <int DIM, int CG, bool F32, int OUT>
 __global__ __launch_bounds__(kThreads) void k_conv(CnnGeom g, const void* __restrict__ in, int cin,
                                                    const uint16_t* __restrict__ w,
@@ -172,10 +275,12 @@ __global__ __launch_bounds__(kThreads) void k_conv(CnnGeom g, const void* __rest
   const int cgo = chan_group(cout);
   stage<DIM, CG, F32, 1>(g, t, in, cin, sh);
   __syncthreads();
-  constexpr int GROUPS = C::TX / 16 * C::TY * C::TZ;
+  // a wave takes one half of every second row of points
+  const int wu = __builtin_amdgcn_readfirstlane(wv);
+  const int lx = (wu & 1) * 16 + m, x = t.x + lx;
 #pragma unroll 2
-  for (int q = wv; q < GROUPS; q += kThreads / 64) {
-    const int lx = (q & 1) * 16 + m, ly = (q >> 1) % C::TY, lz = (q >> 1) / C::TY;
+  for (int i = 0; i < C::TY * C::TZ / 2; ++i) {
+    const int row = (wu >> 1) + 2 * i, ly = row % C::TY, lz = row / C::TY;
     const uint16_t* src = sh + ((lz * C::SY + ly) * C::SX + lx) * CG;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -196,24 +301,135 @@ __global__ __launch_bounds__(kThreads) void k_conv(CnnGeom g, const void* __rest
                                                     __builtin_bit_cast(bf16x8, v), acc, 0, 0, 0);
     }
     // acc[e] = channel 4 kg + e of point m of the group
-    const int x = t.x + lx, y = t.y + ly, z = t.z + lz;
-    if (x >= g.nx || y >= g.ny || z >= g.nz) continue;
+    const int y = t.y + ly, z = t.z + lz;  // uniform
+    if (y >= g.ny || z >= g.nz) continue;
     const long p = t.base + ((long)z * g.ny + y) * g.nx + x;
-    if constexpr (OUT == kOutF32) {
-      float* o = static_cast<float*>(out) + p * cout;
+    if (x < g.nx) put<OUT>(acc + b4, out, p, kg, cout, cgo, mask);
+  }
+}
+
+// At most 8 output channels: the 16 rows of the A operand are the channels of
+// two neighbouring points, (s, co) = (row / 8, row % 8), its K dimension the four
+// taps dx = 0 .. 3 that the pair sees per tap row (dy, dz) (weight 0 where the
+// point does not see the tap), and a column is a pair of points.  A row of 32
+// points is one group: 9 MFMAs and LDS reads with 8 input channels where one
+// point per column takes 14, and all offsets are compile-time ones plus the
+// lane's.
+// Infinities and NaNs must not reach a point that does not see them through a
+// weight of 0: where a result is NaN the group is formed again, once per point
+// of the pair, with the fourth tap zeroed.
+// A block stays for several tiles (four blocks per CU): weights and set-up once,
+// the next tile's loads in flight during the products.
+// Bound: LDS reads, vector and scalar issue and MFMA take 2 to 3 us each of a
+// tile's 5.5 us; 128^3, 4 -> 8 -> 8 -> 3 channels: 25 + 22 + 22 us, one point
+// per column and one tile per block 34 + 31 + 29 us.
+template <int DIM, int CG, bool F32, int OUT>
+__global__ __launch_bounds__(kThreads, CG == 16 ? 2 : 4) void k_conv_pair(CnnGeom g, const void* __restrict__ in,
+                                                        int cin, const uint16_t* __restrict__ w,
+                                                        const float* __restrict__ bias,
+                                                        void* __restrict__ out, int cout,
+                                                        const uint16_t* __restrict__ mask,
+                                                        const int* __restrict__ skip1,
+                                                        const int* __restrict__ skip2) {
+  typedef CTile<DIM> C;
+  if ((skip1 && *skip1) || (skip2 && *skip2)) return;
+  constexpr int R = C::TAPS / 3;  // tap rows
+  constexpr int NM = CG == 4 ? (R + 1) / 2 : (CG == 8 ? R : 2 * R);
+  __shared__ __align__(16) uint16_t sh[2][C::N * CG];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, kg = lane >> 4;
+  const unsigned tiles = unsigned(tile_count<DIM>(g));
+  const TileRange tr = my_tiles(tiles);
+  if (tr.first >= tr.end) return;
+  TileAt t = tile_at<DIM>(g, tr.first);
+  Stage<DIM, CG, F32, 1> st;
+  st.fetch(g, t, in, cin);
+  // K values of the lane in MFMA j.  CG = 4: taps dx, dx + 1 of tap row 2 j +
+  // (kg >> 1); CG = 8: tap kg of row j; CG = 16: half of the channels of tap
+  // 2 (j & 1) + (kg >> 1) of row j >> 1
+  auto tap_row = [&](int j) { return CG == 4 ? 2 * j + (kg >> 1) : (CG == 8 ? j : j >> 1); };
+  auto tap_dx = [&](int j) { return CG == 4 ? 2 * (kg & 1) : (CG == 8 ? kg : 2 * (j & 1) + (kg >> 1)); };
+  constexpr auto row_off = [](int r) { return ((r / 3) * C::SY + r % 3) * C::SX; };
+  s16x8 wr[NM];
+  {
+    const int sft = m >> 3, co = m & 7;
+    auto weight = [&](int r, int dx, int ch) {
+      const int d = dx - sft;
+      const bool on = r < R && unsigned(d) < 3u;
+      return w + (on ? ((r * 3 + d) * 256 + co * 16 + ch) : 0);
+    };
+    auto seen = [&](int r, int dx) { return r < R && unsigned(dx - sft) < 3u; };
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (4 * kg + e < cout) o[4 * kg + e] = acc[e] + b4[e];
-    } else if (4 * kg < cgo) {
-      s16x4 h, mk = {0, 0, 0, 0};
-      if (OUT == kOutMaskBf16) mk = *reinterpret_cast<const s16x4*>(mask + p * cgo + 4 * kg);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float v = acc[e] + b4[e];
-        const bool pos = OUT == kOutReluBf16 ? v > 0.f : mk[e] > 0;  // sign bit: <= 0
-        h[e] = pos && 4 * kg + e < cout ? short(f2bf(v)) : short(0);
+    for (int j = 0; j < NM; ++j) {
+      const int r = tap_row(j), dx = tap_dx(j), ch = CG == 16 ? 8 * (kg & 1) : 0;
+      if constexpr (CG == 4) {
+        s16x4 a = *reinterpret_cast<const s16x4*>(weight(r, dx, 0));
+        s16x4 b = *reinterpret_cast<const s16x4*>(weight(r, dx + 1, 0));
+        a = seen(r, dx) ? a : s16x4{0, 0, 0, 0};
+        b = seen(r, dx + 1) ? b : s16x4{0, 0, 0, 0};
+        wr[j] = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+      } else {
+        const s16x8 a = *reinterpret_cast<const s16x8*>(weight(r, dx, ch));
+        wr[j] = seen(r, dx) ? a : s16x8{0, 0, 0, 0, 0, 0, 0, 0};
       }
-      *reinterpret_cast<s16x4*>(static_cast<uint16_t*>(out) + p * cgo + 4 * kg) = h;
+    }
+  }
+  const int c4 = kg & 1, px = 2 * m + (kg >> 1);  // the lane's channels and point
+  f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
+  if (bias) b4 = *reinterpret_cast<const f32x4*>(bias + 4 * c4);
+  const int cgo = chan_group(cout);
+  // drop: 0 none, 1 the tap that the first point of the pair does not see, 2
+  // that of the second
+  auto group = [&](const uint16_t* src, int drop) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NM; ++j) {
+      const int r = tap_row(j), dx = tap_dx(j);
+      // the last tap row of CG = 4 is half empty: weights 0 on row 0
+      const int ro = CG == 4 ? ((kg >> 1) ? row_off(2 * j + 1 < R ? 2 * j + 1 : 0) : row_off(2 * j))
+                             : row_off(CG == 8 ? j : j >> 1);
+      s16x8 v = *reinterpret_cast<const s16x8*>(src + (ro + dx) * CG + (CG == 16 ? 8 * (kg & 1) : 0));
+      if (drop) {
+        const int gone = drop == 1 ? 3 : 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (r >= R || dx + (CG == 4 ? e / 4 : 0) == gone) v[e] = 0;
+      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[j]),
+                                                    __builtin_bit_cast(bf16x8, v), acc, 0, 0, 0);
+    }
+    return acc;
+  };
+  // the next tile's loads are in flight while this one is computed; its LDS
+  // was last read before the barrier
+  int buf = 0;
+  for (unsigned tl = tr.first; tl < tr.end; tl += tr.step, buf ^= 1) {
+    st.store(sh[buf]);
+    __syncthreads();
+    const TileAt cur = t;
+    if (tl + tr.step < tr.end) {
+      t = tile_at<DIM>(g, tl + tr.step);
+      st.fetch(g, t, in, cin);
+    }
+#pragma unroll 1
+    for (int i = 0; i < C::TY * C::TZ / 4; ++i) {
+      const int ly = DIM == 3 ? wv : wv + 4 * i, lz = DIM == 3 ? i : 0;
+      static_assert(DIM == 2 || (C::TY == 4 && C::TZ == 4), "a wave per row of a plane");
+      const uint16_t* src = sh[buf] + ((lz * C::SY + ly) * C::SX + 2 * m) * CG;
+      f32x4 acc = group(src, 0);
+      const float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+      if (__any(!(sum == sum))) {
+        // (reads LDS again: its values are not kept for this path)
+        asm volatile("" ::: "memory");
+        const f32x4 a = group(src, 1);
+        asm volatile("" ::: "memory");
+        const f32x4 b = group(src, 2);
+        acc = kg < 2 ? a : b;
+      }
+      const int x = cur.x + px, y = cur.y + ly, z = cur.z + lz;  // y, z uniform
+      if (y >= g.ny || z >= g.nz) continue;
+      const long p = cur.base + ((long)z * g.ny + y) * g.nx + x;
+      if (x < g.nx) put<OUT>(acc + b4, out, p, c4, cout, cgo, mask);
     }
   }
 }
@@ -346,20 +562,27 @@ __global__ __launch_bounds__(kThreads) void k_wgrad_reduce(const float* __restri
   if (tap < taps && ci < cin) flat[(tap * cin + ci) * cout + o] = t;
 }
 
+constexpr unsigned kPairBlocks = 1024;  // four per CU, which fit
+
 template <int DIM, int CG, bool F32>
 void launch_conv(hipStream_t s, const CnnGeom& g, const ConvIn& in, const uint16_t* w,
                  const float* bias, ConvOut mode, void* out, int cout, const uint16_t* mask,
                  const int* skip1, const int* skip2) {
   const unsigned blocks = unsigned(tile_count<DIM>(g));
+  const bool pair = cout <= 8;
+  const unsigned grid = pair ? std::min((blocks + 7) / 8 * 8, kPairBlocks) : blocks;
+  auto go = [&](auto kernel) {
+    kernel<<<grid, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
+  };
   switch (mode) {
     case kOutReluBf16:
-      k_conv<DIM, CG, F32, kOutReluBf16><<<blocks, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
+      pair ? go(k_conv_pair<DIM, CG, F32, kOutReluBf16>) : go(k_conv<DIM, CG, F32, kOutReluBf16>);
       break;
     case kOutF32:
-      k_conv<DIM, CG, F32, kOutF32><<<blocks, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
+      pair ? go(k_conv_pair<DIM, CG, F32, kOutF32>) : go(k_conv<DIM, CG, F32, kOutF32>);
       break;
     case kOutMaskBf16:
-      k_conv<DIM, CG, F32, kOutMaskBf16><<<blocks, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
+      pair ? go(k_conv_pair<DIM, CG, F32, kOutMaskBf16>) : go(k_conv<DIM, CG, F32, kOutMaskBf16>);
       break;
   }
 }

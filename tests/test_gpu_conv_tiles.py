@@ -15,7 +15,7 @@ SHAPES = {2: [(1, 16, 32), (2, 17, 33), (3, 1, 1), (1, 15, 70)],
           3: [(1, 4, 4, 32), (2, 5, 5, 33), (1, 1, 1, 1), (1, 3, 9, 31), (1, 8, 8, 64)]}
 
 
-@pytest.mark.parametrize("channels", [(4, 8), (3, 2), (8, 5), (16, 16)])
+@pytest.mark.parametrize("channels", [(4, 8), (3, 2), (8, 5), (16, 16), (12, 7)])
 @pytest.mark.parametrize("dim,shape", [(d, s) for d in SHAPES for s in SHAPES[d]])
 def test_one_layer_at_tile_edges(dim, shape, channels):
     import torch
@@ -42,3 +42,33 @@ def test_one_layer_at_tile_edges(dim, shape, channels):
         g, dx = net.backward(dev(x, shift), dev(dy, shift))
         assert np.linalg.norm(g - gr) <= 1e-5 * np.linalg.norm(gr)
         assert np.linalg.norm(dx.cpu().numpy() - dxr) <= 1e-5 * np.linalg.norm(dxr)
+
+
+@pytest.mark.parametrize("channels", [(4, 8), (8, 3), (16, 5), (8, 16)])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_non_finite_inputs_stay_local(dim, channels):
+    """An infinity or NaN reaches the points whose taps see it and no other:
+    these are the same bits as without it (the two points of a pair share
+    their taps inside the kernel)."""
+    import itertools
+
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] conv non-finite", dim, channels, flush=True)
+    shape = (1, 18, 66) if dim == 2 else (1, 6, 9, 66)
+    net = gk.CNN(dim, channels, seed=5)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn(shape + (channels[0],), generator=gen, device="cuda")
+    n = shape[1:]
+    spots = [tuple([n[a] // 2 for a in range(dim - 1)] + [i]) for i in (0, 7, 20, 31, 32, 45, n[-1] - 1)]
+    bad, near = x.clone(), np.zeros(n, bool)
+    for q, p in enumerate(spots):
+        bad[(0,) + p + (q % channels[0],)] = (float("inf"), float("-inf"), float("nan"))[q % 3]
+        x[(0,) + p + (q % channels[0],)] = 0.0
+        for d in itertools.product((-1, 0, 1), repeat=dim):
+            at = tuple(a + b for a, b in zip(p, d))
+            if all(0 <= a < b for a, b in zip(at, n)):
+                near[at] = True
+    y, z = net.forward(x)[0].cpu().numpy(), net.forward(bad)[0].cpu().numpy()
+    assert np.array_equal(y[~near], z[~near])
+    assert not np.isfinite(z[near]).any()
