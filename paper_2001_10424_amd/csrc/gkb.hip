@@ -114,6 +114,11 @@ dim3 transfer_grid(const Grid& g) {
   return dim3((maxplane + kBlock - 1) / kBlock, 1, g.dim * g.nze);
 }
 
+dim3 prolong_grid(const Grid& g) {
+  const dim3 t = transfer_grid(g);
+  return dim3(t.x, 1, g.dim * prolong_chunks(g));
+}
+
 template <typename T>
 struct DevArr {
   T* p = nullptr;
@@ -386,9 +391,13 @@ template <typename T>
 void edge_step(gkb_ctx* c, Level<T>& L, const T* b, T* x, const PcgState* st) {
   hipStream_t s = c->cs;
   face_op<T, kResid>(c, L.op, L.fl, x, b, L.rb, T(0), nullptr, st);
-  const dim3 cg = cell_grid(L.g);
-  if (L.g.dim == 2) k_edge_smooth<T, 2><<<cg, kBlock, 0, s>>>(L.g, L.rb, L.edinv, T(L.omega_e), x, st);
-  else k_edge_smooth<T, 3><<<cg, kBlock, 0, s>>>(L.g, L.rb, L.edinv, T(L.omega_e), x, st);
+  if (L.g.dim == 2) {
+    k_edge_smooth2<T><<<cell_grid(L.g), kBlock, 0, s>>>(L.g, L.rb, L.edinv, T(L.omega_e), x, st);
+  } else {
+    int kz = 0;
+    const dim3 grid = edge_grid(L.g, &kz);
+    k_edge_smooth3<T><<<grid, kEdgeThreads, 0, s>>>(L.g, L.rb, L.edinv, T(L.omega_e), x, st, kz);
+  }
 }
 
 // first smoothing sweep from a zero guess, x = omega D^-1 b, from 1 / D
@@ -523,7 +532,7 @@ void vcycle(gkb_ctx* c, Inner<T>& in, int l, const T* b, T* x, double* dot_parti
     cur = o;
     i0 = 1;
   } else {
-    const dim3 fg = transfer_grid(L.g);
+    const dim3 fg = prolong_grid(L.g);
     if (L.g.dim == 2) {
       if (sm) k_prolong_add<T, 2, true><<<fg, kBlock, 0, s>>>(L.g, Lc.g, Lc.x, it, st);
       else k_prolong_add<T, 2, false><<<fg, kBlock, 0, s>>>(L.g, Lc.g, Lc.x, it, st);
