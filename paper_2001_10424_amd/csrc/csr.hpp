@@ -40,8 +40,8 @@ __device__ __forceinline__ T sget(const T* s, int i) {
 // Blocks of the row kernels: one row per thread up to 4096 blocks.  A row is a
 // chain of dependent loads (row pointer, column, x), so these kernels live on
 // rows in flight: 40k rows in blocks of four rows per thread left 39 blocks
-// on 256 compute units (product 14.7 us; one row per thread and the gather
-// below 4.0 us).
+// on 256 compute units (b - M x 18.6 us; one row per thread and the gather
+// below 5.7 us).
 inline int csr_blocks(int n) { return n <= kBlock ? 1 : (n - 1) / kBlock + 1 < 4096 ? (n - 1) / kBlock + 1 : 4096; }
 
 // sum of val_e f(col_e) over row i, in the order of the entries; eight
