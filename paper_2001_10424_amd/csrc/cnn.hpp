@@ -20,8 +20,6 @@
 
 namespace gkb {
 
-constexpr int kMaxLayers = 8;
-
 // flat FP32 layer parameters -> BF16 forward weights wf[t][co][ci], dgrad
 // weights wd[t][ci][co] taken from the mirrored tap, FP32 bias[16]
 __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ flat, int taps,
@@ -265,7 +263,8 @@ int cnn_backward(gkb_cnn* n, const gkb::CnnGeom& g, const gkb::ConvIn& x, const 
                  float* dx) {
   int rc = cnn_prepare_weights(n);
   if (rc) return rc;
-  const size_t need = gkb::wgrad_part_floats(n->dim, g);
+  size_t need = 0;
+  for (int l = 0; l < n->L; ++l) need += gkb::wgrad_part_floats(n->dim, g, n->ch[l]);
   if (need > n->wcap) {
     if (n->wpart) (void)hipFree(n->wpart);
     n->wpart = nullptr;
@@ -276,9 +275,12 @@ int cnn_backward(gkb_cnn* n, const gkb::CnnGeom& g, const gkb::ConvIn& x, const 
   gkb::ConvIn dz = dy;
   // dz0 may hold the output gradient: the hidden ones start in dz1
   uint16_t *cur = n->dz1, *other = n->dz0;
+  gkb::WgradSum sum;
+  float* part = n->wpart;
   for (int l = n->L - 1; l >= 0; --l) {
     const gkb::ConvIn a = l == 0 ? x : gkb::ConvIn{n->act[l], n->ch[l], false};
-    gkb::wgrad_layer(n->s, n->dim, g, a, dz, n->wpart, n->grad + n->off[l]);
+    gkb::wgrad_layer(n->s, n->dim, g, a, dz, part, n->grad + n->off[l], sum);
+    part += gkb::wgrad_part_floats(n->dim, g, n->ch[l]);
     const uint16_t* wd = n->wd + (size_t)l * n->taps * 256;
     // the adjoint convolution reads the layer's output channels
     if (l > 0) {
@@ -290,6 +292,7 @@ int cnn_backward(gkb_cnn* n, const gkb::CnnGeom& g, const gkb::ConvIn& x, const 
       gkb::conv_layer(n->s, n->dim, g, dz, wd, nullptr, gkb::kOutF32, dx, n->ch[0], nullptr);
     }
   }
+  gkb::wgrad_finish(n->s, n->dim, sum);
   CNNCK(hipGetLastError());
   return GKB_OK;
 }

@@ -535,13 +535,20 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(CnnGeom g, const void* __res
 // Sum the block partials in a fixed order into the flat layer gradient
 // W[tap][ci][co], b[co]: a block takes 16 consecutive partial entries, its 16
 // thread groups sum the sets b = grp, grp + 16, ..., and the 16 group sums are
-// added in order.
+// added in order.  One launch for all layers of a network: a layer's sum is
+// one dependent trip to memory of 4.7 us that leaves most of the chip idle.
+// Backward of three layers at 64^3 x 2 points: 146.7 -> 142.9 us (mean of three
+// comparisons; 145.8-147.3 against 142.6-143.1).
 constexpr int kRedOut = 16;
-__global__ __launch_bounds__(kThreads) void k_wgrad_reduce(const float* __restrict__ part, int nblk,
-                                                           int nt, int cg, int taps, int cin,
-                                                           int cout, float* __restrict__ flat) {
+__global__ __launch_bounds__(kThreads) void k_wgrad_reduce(WgradSum ws, int taps) {
+  int la = 0;
+  while (la + 1 < ws.layers && int(blockIdx.x) >= ws.first[la + 1]) ++la;
+  const WgradLayer& l = ws.l[la];
+  const int nblk = ws.nblk, nt = l.nt, cg = l.cg, cin = l.cin, cout = l.cout;
+  const float* __restrict__ part = l.part;
+  float* __restrict__ flat = l.flat;
   const int o = threadIdx.x % kRedOut, grp = threadIdx.x / kRedOut;
-  const int np = (nt + 1) * 256, e = blockIdx.x * kRedOut + o;
+  const int np = (nt + 1) * 256, e = (int(blockIdx.x) - ws.first[la]) * kRedOut + o;
   float s = 0.f;
 #pragma unroll 8
   for (int b = grp; b < nblk; b += kThreads / kRedOut) s += part[(size_t)b * np + e];
@@ -606,7 +613,7 @@ void wgrad_fz(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& 
 
 template <int DIM, int CG>
 void wgrad_cg(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& dz, float* part,
-              float* flat) {
+              float* flat, WgradSum& sum) {
   const int nblk = wgrad_blocks(DIM, g), cz = chan_group(dz.c);
   // FP32 activations are the network's input only
   if (act.f32) {
@@ -619,17 +626,19 @@ void wgrad_cg(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& 
     else wgrad_fz<DIM, CG, 16, false>(s, g, act, dz, part, nblk);
   }
   constexpr int nt = wgrad_tiles<DIM, CG>();
-  k_wgrad_reduce<<<(nt + 1) * 256 / kRedOut, kThreads, 0, s>>>(part, nblk, nt, CG,
-                                                               CTile<DIM>::TAPS, act.c, dz.c, flat);
+  sum.nblk = nblk;
+  sum.l[sum.layers] = WgradLayer{part, flat, nt, CG, act.c, dz.c};
+  sum.first[sum.layers + 1] = sum.first[sum.layers] + (nt + 1) * 256 / kRedOut;
+  ++sum.layers;
 }
 
 template <int DIM>
 void wgrad_dim(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& dz, float* part,
-               float* flat) {
+               float* flat, WgradSum& sum) {
   const int cg = chan_group(act.c);
-  if (cg == 4) wgrad_cg<DIM, 4>(s, g, act, dz, part, flat);
-  else if (cg == 8) wgrad_cg<DIM, 8>(s, g, act, dz, part, flat);
-  else wgrad_cg<DIM, 16>(s, g, act, dz, part, flat);
+  if (cg == 4) wgrad_cg<DIM, 4>(s, g, act, dz, part, flat, sum);
+  else if (cg == 8) wgrad_cg<DIM, 8>(s, g, act, dz, part, flat, sum);
+  else wgrad_cg<DIM, 16>(s, g, act, dz, part, flat, sum);
 }
 
 }  // namespace
@@ -653,15 +662,22 @@ int wgrad_blocks(int dim, const CnnGeom& g) {
   return int(std::min<long>(tiles, 512));
 }
 
-size_t wgrad_part_floats(int dim, const CnnGeom& g) {
-  const int nt = dim == 2 ? wgrad_tiles<2, 16>() : wgrad_tiles<3, 16>();
+size_t wgrad_part_floats(int dim, const CnnGeom& g, int cin) {
+  const int cg = chan_group(cin), taps = dim == 2 ? CTile<2>::TAPS : CTile<3>::TAPS;
+  const int nt = (taps * cg + 15) / 16;
   return (size_t)wgrad_blocks(dim, g) * (nt + 1) * 256;
 }
 
 void wgrad_layer(hipStream_t s, int dim, const CnnGeom& g, const ConvIn& act, const ConvIn& dz,
-                 float* part, float* flat) {
-  if (dim == 2) wgrad_dim<2>(s, g, act, dz, part, flat);
-  else wgrad_dim<3>(s, g, act, dz, part, flat);
+                 float* part, float* flat, WgradSum& sum) {
+  if (dim == 2) wgrad_dim<2>(s, g, act, dz, part, flat, sum);
+  else wgrad_dim<3>(s, g, act, dz, part, flat, sum);
+}
+
+void wgrad_finish(hipStream_t s, int dim, const WgradSum& sum) {
+  if (sum.layers == 0) return;
+  k_wgrad_reduce<<<sum.first[sum.layers], kThreads, 0, s>>>(
+      sum, dim == 2 ? CTile<2>::TAPS : CTile<3>::TAPS);
 }
 
 }  // namespace gkb

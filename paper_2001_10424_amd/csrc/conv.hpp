@@ -22,6 +22,8 @@ __host__ __device__ inline uint16_t f2bf(float f) {
 }
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
+constexpr int kMaxLayers = 8;
+
 struct CnnGeom {
   int nx, ny, nz, batch;
   long P;  // nx * ny * nz * batch
@@ -48,12 +50,25 @@ void conv_layer(hipStream_t s, int dim, const CnnGeom& g, const ConvIn& in, cons
                 const float* bias, ConvOut mode, void* out, int cout, const uint16_t* mask,
                 const int* skip1 = nullptr, const int* skip2 = nullptr);
 
-// weight gradient of one layer in the flat parameter layout:
+// weight gradient of the layers in the flat parameter layout:
 // flat[tap][ci][co] = sum_p act[p + off(tap)][ci] dz[p][co], then
-// flat[..][co] = sum_p dz[p][co]; part: wgrad_part_floats() floats of scratch
+// flat[..][co] = sum_p dz[p][co].  wgrad_layer leaves a layer's block partials
+// in part (wgrad_part_floats() floats for cin input channels, kept until
+// wgrad_finish) and notes it in sum; wgrad_finish adds up all layers at once.
+struct WgradLayer {
+  const float* part;
+  float* flat;
+  int nt, cg, cin, cout;
+};
+struct WgradSum {
+  int layers = 0, nblk = 0;
+  int first[kMaxLayers + 1] = {0};  // first block of each layer's reduction
+  WgradLayer l[kMaxLayers];
+};
 int wgrad_blocks(int dim, const CnnGeom& g);
-size_t wgrad_part_floats(int dim, const CnnGeom& g);
+size_t wgrad_part_floats(int dim, const CnnGeom& g, int cin);
 void wgrad_layer(hipStream_t s, int dim, const CnnGeom& g, const ConvIn& act, const ConvIn& dz,
-                 float* part, float* flat);
+                 float* part, float* flat, WgradSum& sum);
+void wgrad_finish(hipStream_t s, int dim, const WgradSum& sum);
 
 }  // namespace gkb

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import cnn_ref
-from test_gpu_cnn import bf16
+from test_gpu_cnn import _ref_backward_bf16, bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +72,43 @@ def test_non_finite_inputs_stay_local(dim, channels):
     y, z = net.forward(x)[0].cpu().numpy(), net.forward(bad)[0].cpu().numpy()
     assert np.array_equal(y[~near], z[~near])
     assert not np.isfinite(z[near]).any()
+
+
+def _integer_network(dim, channels, rng):
+    """Flat parameters: every output channel takes one tap of one input
+    channel with weight 1 or -1, biases 0 to 2."""
+    parts = []
+    taps = 3 ** dim
+    for cin, cout in zip(channels[:-1], channels[1:]):
+        W = np.zeros((taps, cin, cout))
+        for co in range(cout):
+            W[rng.integers(taps), co % cin, co] = 1.0
+        parts += [W.ravel(), rng.integers(0, 3, cout).astype(float)]
+    return np.concatenate(parts)
+
+
+@pytest.mark.parametrize("channels", [(4, 8, 16, 3, 8, 12, 5, 9, 2), (16, 4, 1), (1, 16, 8)])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_layers_reduced_together(dim, channels):
+    """The weight gradients of all layers are added up in one launch: every
+    layer's block of the gradient, up to the eight layers a network can have
+    and with channel groups of 4, 8 and 16 side by side.  All stored values
+    are integers below 256 (exact in BF16) and all sums below 2^24 (exact in
+    FP32), so the gradients have to be equal."""
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] conv layers", dim, channels, flush=True)
+    rng = np.random.default_rng(4)
+    shape = SHAPES[dim][1]
+    params = _integer_network(dim, channels, rng)
+    x = rng.integers(-2, 3, shape + (channels[0],)).astype(np.float32)
+    dy = rng.integers(-1, 2, shape + (channels[-1],)).astype(np.float32)
+    want, dxw = _ref_backward_bf16(x, params, dim, channels, dy)
+    assert np.abs(want).max() < 2 ** 24
+    assert all(W.any() and b.any() for W, b in cnn_ref.unflatten(want, dim, channels))
+    net = gk.CNN(dim, channels, seed=6)
+    net.params = params.astype(np.float32)
+    for _ in range(2):
+        got, dx = net.backward(torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda())
+        assert np.array_equal(np.asarray(got, np.float64), want)
+        assert np.array_equal(dx.cpu().numpy().astype(np.float64), dxw)
