@@ -536,8 +536,9 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(CnnGeom g, const void* __res
 // W[tap][ci][co], b[co]: a block takes 16 consecutive partial entries, its 16
 // thread groups sum the sets b = grp, grp + 16, ..., and the 16 group sums are
 // added in order.  One launch for all layers of a network: a layer's sum is
-// one dependent trip to memory of 4.7 us that leaves most of the chip idle.
-// Backward of three layers at 64^3 x 2 points: 146.7 -> 142.9 us (mean of three
+// one dependent trip to memory of 4.7 us that leaves most of the chip idle;
+// three together take 8.9 us.  Backward
+// of three layers at 64^3 x 2 points: 146.7 -> 142.9 us (mean of three
 // comparisons; 145.8-147.3 against 142.6-143.1).
 constexpr int kRedOut = 16;
 __global__ __launch_bounds__(kThreads) void k_wgrad_reduce(WgradSum ws, int taps) {
