@@ -1520,8 +1520,9 @@ int setup_impl(gkb_ctx* c, const gkb_grid* grid, const double* visc, double eta,
   for (int l = 0; l < L; ++l) {
     maxp = std::max(maxp, face_launch(c->grids[l], 4, c->opt.stencil).nparts);
     maxp = std::max(maxp, face_launch(c->grids[l], 4, 1).nparts);
-    maxp = std::max(maxp, std::max(level_legs(c, c->grids[l], 4).nblocks,
-                                   level_legs(c, c->grids[l], 8).nblocks));
+    if (l < L - 1)  // the coarsest level has no legs
+      maxp = std::max(maxp, std::max(level_legs(c, c->grids[l], 4).nblocks,
+                                     level_legs(c, c->grids[l], 8).nblocks));
     const dim3 tg = transfer_grid(c->grids[l]);  // learned unpack partials
     maxp = std::max(maxp, (int)(tg.x * tg.z));
     maxp = std::max(maxp, cell_parts(c->grids[l]));

@@ -24,6 +24,24 @@ constexpr int kMarchWide = 16, kMarchSquare = 17;
 inline bool marches(const LegPlan& p) { return p.tile >= kMarchWide; }
 LegPlan march_plan(const Grid& g, int elem, bool smooth);
 
+// Planes per block of a march over nz planes by `columns` blocks per plane
+// (even: a chunk starts on a coarse plane).  A block has a compute unit for
+// itself, and a chunk costs about 9 planes more than it has, so the shortest sum
+// of rounds is taken; four planes are the least, also where a grid has fewer.
+inline int march_planes(int columns, int nz) {
+  int best_tz = 4;
+  long best = -1;
+  for (int tz = 4; tz < nz + 2; tz += 2) {
+    const int chunks = (nz + tz - 1) / tz;
+    const long cost = ((long)columns * chunks + 255) / 256 * (tz + 9);
+    if (best < 0 || cost < best) {
+      best = cost;
+      best_tz = tz;
+    }
+  }
+  return best_tz;
+}
+
 // what both legs read of a level
 template <typename T>
 struct LegLevel {

@@ -696,22 +696,12 @@ __global__ __launch_bounds__(TL::NT) void k_march_up(LegLevel<T> L, Geo G, const
 typedef MTile<32, 16, 768> MWide;
 typedef MTile<16, 16, 448> MSquare;
 
-// chunks of planes: a block has a compute unit for itself, and a chunk costs
-// about 9 planes more than it has, so the shortest sum of rounds is taken
 template <class TL>
 LegPlan plan_march(const Grid& g, int id) {
   const int gx = (g.n[0] + TL::TX - 1) / TL::TX, gy = (g.n[1] + TL::TY - 1) / TL::TY;
   LegPlan p;
   p.tile = id;
-  long best = -1;
-  for (int tz = 4; tz < g.n[2] + 2; tz += 2) {
-    const int chunks = (g.n[2] + tz - 1) / tz;
-    const long cost = (long)((gx * gy * chunks + 255) / 256) * (tz + 9);
-    if (best < 0 || cost < best) {
-      best = cost;
-      p.tz = tz;
-    }
-  }
+  p.tz = march_planes(gx * gy, g.n[2]);
   p.grid = dim3(gx, gy, (g.n[2] + p.tz - 1) / p.tz);
   p.nblocks = p.grid.x * p.grid.y * p.grid.z;
   return p;

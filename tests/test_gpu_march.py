@@ -50,3 +50,28 @@ def test_marching_legs_match_separate_kernels(name, transfer, precision):
     big = np.abs(out[0] - out[1]).max() / np.abs(out[1]).max()
     print("   relative difference", err, big, flush=True)
     assert err <= 1e3 * eps and big <= 1e4 * eps
+
+
+@pytest.mark.parametrize("n,eta", [((256, 256, 2), 1.0), ((250, 200, 2), 1e3), ((254, 250, 3), 1.0)])
+def test_slabs_too_thin_to_march(n, eta):
+    """Grids of two and three planes with more cells than the box legs take:
+    set up with the Jacobi inner solver, their residual against the oracle
+    (entries of at most 30 products: 64 eps), and refused for multigrid,
+    whose coarsest level they are."""
+    import oracle
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] slab", n, eta, flush=True)
+    g = P.Grid(3, n, 0.5, WALLS, 0)
+    rng = np.random.default_rng(3)
+    mask = g.face_mask()
+    v = [rng.standard_normal(g.m_full) * mask, rng.standard_normal(g.n_cells),
+         rng.standard_normal(g.m_full) * mask, rng.standard_normal(g.n_cells)]
+    s = gk.Solver(g, None, eta, inner="jacobi")
+    dev = [torch.tensor(a, dtype=torch.float64, device="cuda") for a in v]
+    _, rw, rr = s.residual(*dev, want_vectors=True)
+    s.close()
+    for a, b in zip((rw, rr), oracle.saddle_residual(g, *v)[:2]):
+        assert np.abs(a.cpu().numpy() - b).max() <= 64 * 2.0 ** -52 * np.abs(b).max()
+    with pytest.raises(RuntimeError, match="invalid argument"):
+        gk.Solver(g, None, eta, inner="mg")
