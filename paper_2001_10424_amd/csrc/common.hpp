@@ -91,6 +91,34 @@ __device__ __forceinline__ double fold_sum(double v, double* sh) {
   __syncthreads();  // sh may be used again
   return s;
 }
+// The same sum in a kernel whose block 0 may set the flag that its blocks test:
+// a late block's waves can read the flag on either side of that store, so each
+// brings what it read (off) and the block goes by all of them.  Returns
+// false, in every thread, if any wave saw the flag set; else s is the sum.
+template <int BS>
+struct FoldShared {
+  double s[BS / 64];
+  int off[BS / 64];
+};
+template <int BS>
+__device__ __forceinline__ bool fold_sum_if(int off, double v, FoldShared<BS>& sh, double& s) {
+  v = wave_sum(v);
+  off = __any(off);
+  if ((threadIdx.x & 63) == 0) {
+    sh.s[threadIdx.x >> 6] = v;
+    sh.off[threadIdx.x >> 6] = off;
+  }
+  __syncthreads();
+  s = 0.0;
+  int any = 0;
+#pragma unroll
+  for (int w = 0; w < BS / 64; ++w) {
+    s += sh.s[w];
+    any |= sh.off[w];
+  }
+  __syncthreads();  // sh may be used again
+  return any == 0;
+}
 
 // Scalar steps of PCG on the device state (one thread): alpha from p.q;
 // the convergence test on r.r (with rz: also beta, Jacobi path); beta from
@@ -143,8 +171,10 @@ __device__ __forceinline__ void pcg_set_beta(PcgState* st, double rz) {
 // block 0 records it.  No kernel reads a field that it writes itself: the
 // product (A) reads rz_x and fresh and writes rz and beta; the update (X)
 // reads rz and it and writes alpha, rz_x, it_x and fresh; the first V-cycle
-// kernel (C) reads it_x and writes it and the outcome.  done is written by X
-// and C only when every block of them comes to the same end by itself.
+// kernel (C) reads it_x and writes it and the outcome.  done alone is read and
+// written by X and C, where every block comes to the same end by itself; a
+// block that starts late may see it set, and then all of its waves have to
+// (fold_sum_if).
 __device__ __forceinline__ double fold_beta(PcgState* st, double rz_new, bool lead) {
   if (st->fresh) return 0.0;  // p = z: rz is that of the start
   const double b = rz_new / st->rz_x;

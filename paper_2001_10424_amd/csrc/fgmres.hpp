@@ -202,8 +202,8 @@ __device__ __forceinline__ void gm_step_end(PcgState* st, PcgState* cyc, FgmStat
 // pass's result with nb partials of w.w; j = 0: w = r and ||w|| = beta).  With
 // dinv also z_j = D^-1 v_j, and with t (assembled system) t = A'^T z_j, formed
 // from w, so that the product needs no kernel in between.  Blocks that
-// start after block 0 ended the cycle leave their part of v_j unwritten; no
-// kernel reads it then.
+// start after block 0 ended the cycle leave their part of v_j unwritten (all
+// waves of a block or none); no kernel reads it then.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_gm_next(int n, PcgState* st, PcgState* cyc,
                                                     FgmState* fs, const double* __restrict__ part,
@@ -211,16 +211,25 @@ __global__ __launch_bounds__(kBlock) void k_gm_next(int n, PcgState* st, PcgStat
                                                     T* __restrict__ v, const T* __restrict__ dinv,
                                                     T* __restrict__ z, CsrOps<T> o,
                                                     T* __restrict__ t) {
-  if (cyc->done) return;
-  __shared__ double sh[kBlock / 64];
+  __shared__ FoldShared<kBlock> fold;
+  const int done = cyc->done;
+  if (done && j == 0) return;
   const int i0 = blockIdx.x * kBlock + threadIdx.x, step = gridDim.x * kBlock;
   auto at = [&](int k) { return csr_at_row(o, k, [&](int i) { return dinv[i] * w[i]; }); };
-  // the first entries are fetched beside the partials
-  T wi = i0 < n ? w[i0] : T(0), di = dinv && i0 < n ? dinv[i0] : T(0);
-  T ti = t && i0 < o.n ? at(i0) : T(0);
+  T wi = T(0), di = T(0), ti = T(0);
+  double share = 0.0;
+  if (!done) {
+    // the first entries are fetched beside the partials
+    if (i0 < n) wi = w[i0];
+    if (dinv && i0 < n) di = dinv[i0];
+    if (t && i0 < o.n) ti = at(i0);
+    if (j > 0) share = fold_share<kBlock>(part, nb);
+  }
   double hn = fs->beta;
   if (j > 0) {
-    hn = sqrt(fold_sum<kBlock>(fold_share<kBlock>(part, nb), sh));
+    double ww;
+    if (!fold_sum_if<kBlock>(done, share, fold, ww)) return;
+    hn = sqrt(ww);
     if (blockIdx.x == 0) gm_step_end(st, cyc, fs, hn, j - 1, false);
   }
   const T s = T(1.0 / hn);

@@ -587,14 +587,14 @@ __global__ __launch_bounds__(kBlock) void k_pcg_xr_fold(int n, PcgState* st,
                                                         const T* __restrict__ q,
                                                         T* __restrict__ x, T* __restrict__ r,
                                                         double* __restrict__ part_rr) {
+  __shared__ FoldShared<kBlock> fold;
   __shared__ double sh[kBlock / 64];
   const int done = st->done;
   int i = blockIdx.x * kBlock + threadIdx.x;
   const int e = i < n ? i : 0;
   T xi = x[e], pi = p[e], ri = r[e], qi = q[e];
-  const double share = fold_share<kBlock>(part_pq, npq);
-  if (done) return;
-  const double pq = fold_sum<kBlock>(share, sh);
+  double pq;
+  if (!fold_sum_if<kBlock>(done, fold_share<kBlock>(part_pq, npq), fold, pq)) return;
   const T a = T(fold_alpha(st, pq, blockIdx.x == 0 && threadIdx.x == 0));
   double s = 0.0;
   while (i < n) {

@@ -450,13 +450,14 @@ __global__ __launch_bounds__(TL::NT) void k_leg_down(LegLevel<T> L, const T* __r
   a1.load(G, HYB ? b : L.dinv, i0, j0, k0);
   if constexpr (HYB) ed.load(L, i0, j0, k0);
   br.load(G, b, i0, j0, k0);
-  const double share = check.part ? fold_share<TL::NT>(check.part, check.n) : 0.0;
-  if (done) return;
   if (check.part) {  // uniform
-    __shared__ double sh[TL::NT / 64];
-    const double rr = fold_sum<TL::NT>(share, sh);
+    __shared__ FoldShared<TL::NT> fold;
+    double rr;
+    if (!fold_sum_if<TL::NT>(done, fold_share<TL::NT>(check.part, check.n), fold, rr)) return;
     const bool lead = threadIdx.x == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0;
     if (fold_check(check.st, rr, lead)) return;
+  } else if (done) {
+    return;
   }
   const bool special = fill_edges<T, TL, B>(G, E, i0, j0, k0);
   // first sweep from a zero guess

@@ -15,6 +15,7 @@
 #define __forceinline__ inline
 #define __launch_bounds__(...)
 #define __shared__ static
+#define __align__(n) __attribute__((aligned(n)))
 #define __amdgpu_buffer_rsrc_t int
 #define __builtin_amdgcn_make_buffer_rsrc(p, a, b, c) (0)
 #define __builtin_amdgcn_raw_buffer_load_b32(...) (0u)
@@ -23,6 +24,8 @@
 #define __builtin_amdgcn_raw_buffer_store_b64(...) ((void)0)
 
 typedef void* hipStream_t;
+typedef float float2 __attribute__((ext_vector_type(2)));
+typedef double double2 __attribute__((ext_vector_type(2)));
 struct dim3 {
   unsigned x, y, z;
   dim3(unsigned a = 1, unsigned b = 1, unsigned c = 1) : x(a), y(b), z(c) {}
@@ -81,4 +84,9 @@ inline double __shfl(double v, int lane, int) {
 }
 inline double __shfl_xor(double v, int mask, int width) {
   return __shfl(v, (threadIdx.x & 63) ^ mask, width);
+}
+inline int __any(int v) {
+  double any = 0.0;
+  for (int lane = 0; lane < 64; ++lane) any += __shfl(double(v != 0), lane, 64);
+  return any != 0.0;
 }
