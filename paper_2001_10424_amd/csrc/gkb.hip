@@ -364,16 +364,31 @@ void div_axpy(gkb_ctx* c, const Grid& g, const T* x, const T* z, double s1, doub
     k_div_axpy<T, 3><<<cell_grid(g), kBlock, 0, c->cs>>>(g, x, z, s1, s2, t, partial, zz);
 }
 
+bool overlap(const void* a, size_t bytes_a, const void* b, size_t bytes_b) {
+  const char *p = static_cast<const char*>(a), *q = static_cast<const char*>(b);
+  return p < q + bytes_b && q < p + bytes_a;
+}
+
+// res_r may lie on p or g, which blocks of the one pass still read: it is then
+// formed by a pass of its own
 void launch_saddle(const Op<double>& op, bool varmu, const double* g, const double* r,
                    const double* w, const double* p, double* res_w, double* res_r, double* p_rr,
                    double* p_gg, double* p_tt, double* p_zz, hipStream_t s) {
   const SaddleLaunch L = saddle_launch(op.g);
+  const size_t cells = op.g.n_cells * sizeof(double), faces = op.g.m_full * sizeof(double);
+  const bool later = overlap(res_r, cells, p, cells) || overlap(res_r, cells, g, faces);
   auto go = [&](auto kernel) {
-    kernel<<<L.blocks, kSaddleBlock, 0, s>>>(op, g, r, w, p, res_w, res_r, L.kz, L.bx, p_rr, p_gg,
-                                             p_tt, p_zz);
+    kernel<<<L.blocks, kSaddleBlock, 0, s>>>(op, g, r, w, p, res_w, later ? nullptr : res_r, L.kz,
+                                             L.bx, p_rr, p_gg, p_tt, p_zz);
   };
   if (op.g.dim == 2) varmu ? go(k_saddle<2, true>) : go(k_saddle<2, false>);
   else varmu ? go(k_saddle<3, true>) : go(k_saddle<3, false>);
+  if (!later) return;
+  const dim3 grid = cell_grid(op.g);
+  if (op.g.dim == 2)
+    k_div_axpy<double, 2><<<grid, kBlock, 0, s>>>(op.g, w, r, -1.0, 1.0, res_r, nullptr, nullptr);
+  else
+    k_div_axpy<double, 3><<<grid, kBlock, 0, s>>>(op.g, w, r, -1.0, 1.0, res_r, nullptr, nullptr);
 }
 
 int host_sum(gkb_ctx* c, const double* partial, int n, double* out) {

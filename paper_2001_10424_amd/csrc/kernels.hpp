@@ -189,7 +189,8 @@ __device__ __forceinline__ double visc_side(bool in, bool wall, double kap, doub
 constexpr int kSaddleBlock = 512;
 
 // FP64 saddle residual in one pass: res_w = g - W w - A p on the unknown faces
-// (0 elsewhere, may be null), res_r = r - A^T w on the cells (0 at the pin);
+// (0 elsewhere, may be null), res_r = r - A^T w on the cells (0 at the pin; may
+// be null);
 // partials of res_w.res_w, g.g (unknown faces), res_r.res_r, r.r (unpinned
 // cells) to part[0 .. 3][block].
 //
@@ -363,7 +364,7 @@ __global__ __launch_bounds__(kSaddleBlock) void k_saddle(Op<double> op,
         tt += v * v;
         zz += rc * rc;
       }
-      res_r[ic] = v;
+      if (res_r) res_r[ic] = v;
     }
     uB = uC, vB = vC, wB = wC, pB = pC;
     uC = uT, vC = vT, wC = wT;

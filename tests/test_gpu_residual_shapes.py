@@ -57,3 +57,41 @@ def test_residual_matches_oracle(name, varmu):
         assert np.abs(a.cpu().numpy() - b).max() <= eps * max(np.abs(b).max(), 1.0)
     # sums of squares: a few eps per entry and one per addition level
     assert np.allclose(norms, ref_n, rtol=eps, atol=0) and norms2 == norms
+
+
+@pytest.mark.parametrize("name", ["3d_nat", "3d_deep", "2d_odd"])
+def test_results_on_their_inputs(name):
+    """res_w on g, and res_r on r, on p or at the start of g: the same norms,
+    and the residuals of buffers of their own (up to the contraction of a
+    multiply-add: 64 eps of the largest entry)."""
+    import ctypes as C
+
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] residual in place", name, flush=True)
+    grid = GRIDS[name]
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    n = {"g": grid.m_full, "r": grid.n_cells, "w": grid.m_full, "p": grid.n_cells}
+    v = {k: torch.randn(m, generator=gen, dtype=torch.float64, device="cuda") for k, m in n.items()}
+    s = gk.Solver(grid, None, 10.0, inner="jacobi")
+    norms, rw, rr = s.residual(*v.values(), want_vectors=True)
+
+    def call(on_w, on_r, alloc):
+        c = {k: t.clone() for k, t in v.items()}
+        ow = c[on_w] if on_w else None
+        if not alloc:
+            got, _, _ = gk.residual_noalloc(grid, *c.values(), res_w=ow, res_r=c[on_r][:grid.n_cells])
+        else:
+            got = (C.c_double * 4)()
+            rc = gk.library().gkb_residual(s._ctx, *[gk._ptr(t) for t in c.values()], gk._ptr(ow),
+                                           gk._ptr(c[on_r]), got)
+            assert rc == 0
+        return list(got), ow, c[on_r][:grid.n_cells]
+
+    for alloc in (True, False):
+        for on_w, on_r in (("g", "r"), ("g", "p"), (None, "p"), (None, "g")):
+            got, ow, orr = call(on_w, on_r, alloc)
+            assert got == norms
+            assert ow is None or torch.equal(ow, rw)
+            assert float((orr - rr).abs().max()) <= 64 * 2.0 ** -52 * float(rr.abs().max())
+    s.close()
