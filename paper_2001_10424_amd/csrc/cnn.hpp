@@ -410,8 +410,13 @@ int gkb_cnn_forward(gkb_cnn* n, int nx, int ny, int nz, int batch, const float* 
   gkb::CnnGeom g{nx, ny, nz, batch, (long)nx * ny * nz * batch};
   int rc = cnn_reserve(n, g.P);
   if (rc) return rc;
-  rc = cnn_forward(n, g, gkb::ConvIn{x, n->ch[0], true}, y);
+  // a single layer reads x while it writes y: where they overlap, y is formed
+  // in the network's own buffer
+  const size_t bx = g.P * n->ch[0] * sizeof(float), by = g.P * n->ch[n->L] * sizeof(float);
+  const bool own = n->L == 1 && gkb::overlap(x, bx, y, by);
+  rc = cnn_forward(n, g, gkb::ConvIn{x, n->ch[0], true}, own ? n->y : y);
   if (rc) return rc;
+  if (own) CNNCK(hipMemcpyAsync(y, n->y, by, hipMemcpyDeviceToDevice, n->s));
   CNNCK(hipStreamSynchronize(n->s));
   return GKB_OK;
 }
@@ -428,6 +433,13 @@ int gkb_cnn_backward(gkb_cnn* n, int nx, int ny, int nz, int batch, const float*
   const gkb::ConvIn in{x, n->ch[0], true};
   rc = cnn_forward(n, g, in, nullptr);  // the output itself is not needed
   if (rc) return rc;
+  // a single layer reads dy while it writes dx: where they overlap, it reads a
+  // copy (the network's output buffer is free)
+  const size_t bx = g.P * n->ch[0] * sizeof(float), by = g.P * n->ch[n->L] * sizeof(float);
+  if (n->L == 1 && dx && gkb::overlap(dx, bx, dy, by)) {
+    CNNCK(hipMemcpyAsync(n->y, dy, by, hipMemcpyDeviceToDevice, n->s));
+    dy = n->y;
+  }
   rc = cnn_backward(n, g, in, gkb::ConvIn{dy, n->ch[n->L], true}, dx);
   if (rc) return rc;
   if (grad_host) CNNCK(hipMemcpyAsync(grad_host, n->grad, n->np * 4, hipMemcpyDeviceToHost, n->s));

@@ -7,12 +7,20 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+
 #include "mac.hpp"
 
 namespace gkb {
 
 constexpr int kBlock = 256;   // threads per block (4 wave64)
 constexpr int kFinal = 1024;  // threads of the one-block finalisers
+
+// two buffers of the caller share memory
+inline bool overlap(const void* a, size_t bytes_a, const void* b, size_t bytes_b) {
+  const char *p = static_cast<const char*>(a), *q = static_cast<const char*>(b);
+  return p < q + bytes_b && q < p + bytes_a;
+}
 
 // ------------------------------------------------------------- reductions
 

@@ -364,11 +364,6 @@ void div_axpy(gkb_ctx* c, const Grid& g, const T* x, const T* z, double s1, doub
     k_div_axpy<T, 3><<<cell_grid(g), kBlock, 0, c->cs>>>(g, x, z, s1, s2, t, partial, zz);
 }
 
-bool overlap(const void* a, size_t bytes_a, const void* b, size_t bytes_b) {
-  const char *p = static_cast<const char*>(a), *q = static_cast<const char*>(b);
-  return p < q + bytes_b && q < p + bytes_a;
-}
-
 // res_r may lie on p or g, which blocks of the one pass still read: it is then
 // formed by a pass of its own
 void launch_saddle(const Op<double>& op, bool varmu, const double* g, const double* r,

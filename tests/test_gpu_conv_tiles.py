@@ -112,3 +112,31 @@ def test_layers_reduced_together(dim, channels):
         got, dx = net.backward(torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda())
         assert np.array_equal(np.asarray(got, np.float64), want)
         assert np.array_equal(dx.cpu().numpy().astype(np.float64), dxw)
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+def test_one_layer_on_its_own_buffers(dim):
+    """A single layer whose output lies on its input (y on x; dx on dy, and on
+    x): the same bits as in buffers of their own."""
+    import ctypes as C
+
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] conv in place", dim, flush=True)
+    shape = (2, 90, 70) if dim == 2 else (2, 17, 22, 35)
+    net = gk.CNN(dim, (8, 8), seed=3)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    x, dy = (torch.randn(shape + (8,), generator=gen, device="cuda") for _ in range(2))
+    y = net.forward(x)
+    grad, dx = net.backward(x, dy)
+    L, geom = gk.library(), net._geom(x, dim)
+    ptr = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+    a = x.clone()
+    assert L.gkb_cnn_forward(net._h, *geom, ptr(a), ptr(a)) == 0
+    assert torch.equal(a, y)
+    for on_x in (False, True):
+        a, b, g = x.clone(), dy.clone(), np.empty_like(grad)
+        out = a if on_x else b
+        assert L.gkb_cnn_backward(net._h, *geom, ptr(a), ptr(b), ptr(out),
+                                  g.ctypes.data_as(C.c_void_p)) == 0
+        assert torch.equal(out, dx) and np.array_equal(g, grad)
