@@ -1019,6 +1019,23 @@ int gkb_run(gkb_ctx* c, const double* gv, const double* rv, double tol, int dela
   return status;
 }
 
+// z = B r; z may be r: the legs read r around a tile that others write, so the
+// cycle then ends in the context's own vector
+template <typename T>
+int precondition_impl(gkb_ctx* c, const T* r, T* z) {
+  Inner<T>& in = inner_of<T>(c);
+  if (!in.ready) return GKB_EINVAL;
+  const int m = c->g.m_full;
+  if (c->opt.inner == GKB_INNER_JACOBI) {
+    k_pcg_p0<T><<<vec_blocks(m), kBlock, 0, c->cs>>>(m, in.dinv, r, z, in.q, c->part[0]);
+    return GKB_OK;
+  }
+  const bool own = overlap(r, m * sizeof(T), z, m * sizeof(T));
+  vcycle<T>(c, in, 0, r, own ? in.z : z, nullptr, nullptr);
+  if (own) HIPCK(hipMemcpyAsync(z, in.z, m * sizeof(T), hipMemcpyDeviceToDevice, c->cs));
+  return GKB_OK;
+}
+
 // FP64 saddle residual res = [g - W w - A p; r - A^T w] and its norms.  On
 // an assembled system with central scaling the iteration works in the
 // scaled space; user_space = true takes the user's unscaled operators (the
@@ -2120,26 +2137,12 @@ int gkb_precondition(gkb_ctx* c, int precision, const void* r, void* z) {
   if (!c || !r || !z) return GKB_EINVAL;
   HIPCK(hipEventRecord(c->ev, c->us));
   HIPCK(hipStreamWaitEvent(c->cs, c->ev, 0));
-  const int m = c->g.m_full;
-  if (precision == GKB_FP64) {
-    if (!c->in64.ready) return GKB_EINVAL;
-    Inner<double>& in = c->in64;
-    if (c->opt.inner == GKB_INNER_JACOBI)
-      k_pcg_p0<double><<<vec_blocks(m), kBlock, 0, c->cs>>>(m, in.dinv, static_cast<const double*>(r),
-                                                            static_cast<double*>(z), in.q, c->part[0]);
-    else
-      vcycle<double>(c, in, 0, static_cast<const double*>(r), static_cast<double*>(z), nullptr, nullptr);
-  } else if (precision == GKB_MIXED) {
-    if (!c->in32.ready) return GKB_EINVAL;
-    Inner<float>& in = c->in32;
-    if (c->opt.inner == GKB_INNER_JACOBI)
-      k_pcg_p0<float><<<vec_blocks(m), kBlock, 0, c->cs>>>(m, in.dinv, static_cast<const float*>(r),
-                                                           static_cast<float*>(z), in.q, c->part[0]);
-    else
-      vcycle<float>(c, in, 0, static_cast<const float*>(r), static_cast<float*>(z), nullptr, nullptr);
-  } else {
+  if (precision == GKB_FP64)
+    CK(precondition_impl<double>(c, static_cast<const double*>(r), static_cast<double*>(z)));
+  else if (precision == GKB_MIXED)
+    CK(precondition_impl<float>(c, static_cast<const float*>(r), static_cast<float*>(z)));
+  else
     return GKB_EINVAL;
-  }
   HIPCK(hipGetLastError());
   HIPCK(hipStreamSynchronize(c->cs));
   return GKB_OK;

@@ -97,3 +97,28 @@ def test_direction_buffers_alternate_for_any_chunk(n):
     for x, it in out[1:]:
         assert it == out[0][1]
         assert float((x - out[0][0]).norm() / x.norm()) <= (0.0 if n == 32 else 1e-5)
+
+
+@pytest.mark.parametrize("name,smoother,precision", [
+    ("2d_nat", "hybrid", "fp64"), ("3d_medium", "hybrid", "mixed"), ("3d_large", "jacobi", "fp64")])
+def test_precondition_on_its_input(name, smoother, precision):
+    """z on r: the same bits as in a vector of its own."""
+    import ctypes as C
+
+    import torch
+    import paper_2001_10424_amd as gk
+    from paper_2001_10424_amd import _abi
+    print("[case] precondition in place", name, smoother, precision, flush=True)
+    g = GRIDS[name]
+    nu = 1 if smoother == "hybrid" else 2
+    for stencil in (0, 1):
+        s = gk.Solver(g, None, 1e2, inner="mg", stencil=stencil, smoother=smoother, nu_pre=nu,
+                      nu_post=nu, precision=precision)
+        r = _dev(np.random.default_rng(8).standard_normal(g.m_full),
+                 torch.float64 if precision == "fp64" else torch.float32)
+        z = s.precondition(r, precision)
+        p = C.c_void_p(r.data_ptr())
+        prec = _abi.FP64 if precision == "fp64" else _abi.MIXED
+        assert gk.library().gkb_precondition(s._ctx, prec, p, p) == 0
+        assert torch.equal(r, z)
+        s.close()
