@@ -9,6 +9,7 @@
 #include "conv.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace gkb {
 namespace {
@@ -451,12 +452,17 @@ __device__ __forceinline__ s16x4 lds_transposed(const uint16_t* a) {
 // whole points, so it stays aligned.  One more tile with a row of ones gives
 // the bias gradient.  A block sums several tiles of points and writes one set
 // of FP32 partials; k_wgrad_reduce adds the sets in a fixed order.
+// CUT: tiles can reach past the grid.  The points there have dz = 0, but their
+// taps see activations inside it, and 0 times an infinity is no 0: where a
+// block's sums hold a NaN it forms them again without those points (their rows
+// left out, zeros read in a row).  Leaving them out at once, by a mask or by the
+// address, cost 3 to 4 us a layer at 62^3 x 2 points.
 // 64^3 x 2 points: 14 us for 8 x 8 channels and 12 us for 4 x 8; 235 and 142
 // us with single BF16 values gathered from memory.
 template <int DIM, int CG>
 constexpr int wgrad_tiles() { return (CTile<DIM>::TAPS * CG + 15) / 16; }
 
-template <int DIM, int CG, int CGZ, bool FA, bool FZ>
+template <int DIM, int CG, int CGZ, bool FA, bool FZ, bool CUT>
 __global__ __launch_bounds__(kThreads) void k_wgrad(CnnGeom g, const void* __restrict__ act, int ca,
                                                     const void* __restrict__ dz, int cz,
                                                     float* __restrict__ part) {
@@ -464,10 +470,13 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(CnnGeom g, const void* __res
   constexpr int NT = wgrad_tiles<DIM, CG>(), TPT = 16 / CG;  // taps per tile
   constexpr int NZ = C::TX * C::TY * C::TZ;
   constexpr int NR = (NT + 1) * 256;
-  constexpr int BYTES = (C::N * CG + NZ * CGZ) * 2;
+  // CUT: zeros as far as a point's taps reach
+  constexpr int ZERO = CUT ? (((DIM == 3 ? 2 * C::SY : 0) + 2) * C::SX + 3) * CG : 0;
+  constexpr int BYTES = (C::N * CG + NZ * CGZ + ZERO) * 2;
   __shared__ __align__(16) char raw[BYTES > NR * 4 ? BYTES : NR * 4];
   uint16_t* sa = reinterpret_cast<uint16_t*>(raw);
   uint16_t* sz = sa + C::N * CG;
+  uint16_t* zero = sz + NZ * CGZ;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int i = lane & 15, kg = lane >> 4;
   const int piece = i & 3, row = i >> 2;
@@ -481,37 +490,56 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(CnnGeom g, const void* __res
   }
   const int zch = 4 * (piece % (CGZ / 4));  // columns beyond the group are not used
   f32x4 acc[NT + 1];
-#pragma unroll
-  for (int t = 0; t <= NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   s16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = short(0x3F80);
   const unsigned tiles = unsigned(tile_count<DIM>(g));
-  for (unsigned tl = blockIdx.x; tl < tiles; tl += gridDim.x) {
-    const TileAt t = tile_at<DIM>(g, tl);
-    __syncthreads();  // the last tile's reads
-    stage<DIM, CG, FA, 1>(g, t, act, ca, sa);
-    stage<DIM, CGZ, FZ, 0>(g, t, dz, cz, sz);
-    __syncthreads();
-    for (int r = wv; r < C::TY * C::TZ; r += kThreads / 64) {
-      const int ly = r % C::TY, lz = r / C::TY;
-      // K values of the lane: points 8 kg + 0 .. 7 of the row
-      const int x = 8 * kg + row;
-      const uint16_t* pz = sz + (r * C::TX + x) * CGZ + zch;
-      const s16x4 z0 = lds_transposed(pz), z1 = lds_transposed(pz + 4 * CGZ);
-      const s16x8 zv = __builtin_shufflevector(z0, z1, 0, 1, 2, 3, 4, 5, 6, 7);
-      const uint16_t* pa = sa + ((lz * C::SY + ly) * C::SX + x) * CG;
+  // the block's tiles; cut: points past the grid take no part
+  auto sweep = [&](auto cut) {
 #pragma unroll
-      for (int q = 0; q < NT; ++q) {
-        const s16x4 a0 = lds_transposed(pa + off[q]), a1 = lds_transposed(pa + off[q] + 4 * CG);
-        const s16x8 av = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
-                                                         __builtin_bit_cast(bf16x8, zv), acc[q], 0,
-                                                         0, 0);
+    for (int t = 0; t <= NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (unsigned tl = blockIdx.x; tl < tiles; tl += gridDim.x) {
+      const TileAt t = tile_at<DIM>(g, tl);
+      __syncthreads();  // the last tile's reads
+      stage<DIM, CG, FA, 1>(g, t, act, ca, sa);
+      stage<DIM, CGZ, FZ, 0>(g, t, dz, cz, sz);
+      __syncthreads();
+      for (int r = wv; r < C::TY * C::TZ; r += kThreads / 64) {
+        const int ly = r % C::TY, lz = r / C::TY;
+        if (cut && (t.y + ly >= g.ny || t.z + lz >= g.nz)) continue;  // uniform in the wave
+        // K values of the lane: points 8 kg + 0 .. 7 of the row
+        const int x = 8 * kg + row;
+        const uint16_t* pz = sz + (r * C::TX + x) * CGZ + zch;
+        const s16x4 z0 = lds_transposed(pz), z1 = lds_transposed(pz + 4 * CGZ);
+        const s16x8 zv = __builtin_shufflevector(z0, z1, 0, 1, 2, 3, 4, 5, 6, 7);
+        const uint16_t* pa = sa + ((lz * C::SY + ly) * C::SX + x) * CG;
+        const uint16_t* pb = pa + 4 * CG;
+        if constexpr (cut) {
+          if (t.x + x >= g.nx) pa = zero;
+          if (t.x + x + 4 >= g.nx) pb = zero;
+        }
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+          const s16x4 a0 = lds_transposed(pa + off[q]), a1 = lds_transposed(pb + off[q]);
+          const s16x8 av = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
+          acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
+                                                           __builtin_bit_cast(bf16x8, zv), acc[q],
+                                                           0, 0, 0);
+        }
+        acc[NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones),
+                                                          __builtin_bit_cast(bf16x8, zv), acc[NT],
+                                                          0, 0, 0);
       }
-      acc[NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones),
-                                                        __builtin_bit_cast(bf16x8, zv), acc[NT], 0,
-                                                        0, 0);
+    }
+  };
+  sweep(std::false_type{});
+  if constexpr (CUT) {
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) sum += (acc[t][0] + acc[t][1]) + (acc[t][2] + acc[t][3]);
+    if (__syncthreads_or(sum != sum)) {
+      for (int e = threadIdx.x; e < ZERO; e += kThreads) zero[e] = 0;
+      sweep(std::true_type{});
     }
   }
   // the waves add their tiles in a fixed order
@@ -608,8 +636,13 @@ void conv_cg(hipStream_t s, const CnnGeom& g, const ConvIn& in, const uint16_t* 
 template <int DIM, int CG, int CGZ, bool FA>
 void wgrad_fz(hipStream_t s, const CnnGeom& g, const ConvIn& act, const ConvIn& dz, float* part,
               int nblk) {
-  if (dz.f32) k_wgrad<DIM, CG, CGZ, FA, true><<<nblk, kThreads, 0, s>>>(g, act.p, act.c, dz.p, dz.c, part);
-  else k_wgrad<DIM, CG, CGZ, FA, false><<<nblk, kThreads, 0, s>>>(g, act.p, act.c, dz.p, dz.c, part);
+  typedef CTile<DIM> C;
+  const bool cut = g.nx % C::TX || g.ny % C::TY || g.nz % C::TZ;
+  auto go = [&](auto kernel) {
+    kernel<<<nblk, kThreads, 0, s>>>(g, act.p, act.c, dz.p, dz.c, part);
+  };
+  if (dz.f32) cut ? go(k_wgrad<DIM, CG, CGZ, FA, true, true>) : go(k_wgrad<DIM, CG, CGZ, FA, true, false>);
+  else cut ? go(k_wgrad<DIM, CG, CGZ, FA, false, true>) : go(k_wgrad<DIM, CG, CGZ, FA, false, false>);
 }
 
 template <int DIM, int CG>

@@ -140,3 +140,41 @@ def test_one_layer_on_its_own_buffers(dim):
         assert L.gkb_cnn_backward(net._h, *geom, ptr(a), ptr(b), ptr(out),
                                   g.ctypes.data_as(C.c_void_p)) == 0
         assert torch.equal(out, dx) and np.array_equal(g, grad)
+
+
+@pytest.mark.parametrize("channels", [(4, 8), (8, 3), (16, 5), (12, 16)])
+@pytest.mark.parametrize("dim,shape", [(2, (1, 18, 40)), (2, (2, 5, 31)), (3, (1, 5, 6, 33)),
+                                       (3, (2, 4, 4, 32)), (3, (1, 3, 9, 65))])
+def test_non_finite_weight_gradients_stay_local(dim, shape, channels):
+    """An infinite activation in the last column, row or plane makes the
+    gradients of the taps non-finite that combine it with a point of the grid,
+    and no other: these are the same bits as without it (a tile's points past
+    the grid take no part)."""
+    import itertools
+
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] conv weight gradient non-finite", dim, shape, channels, flush=True)
+    net = gk.CNN(dim, channels, seed=5)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn(shape + (channels[0],), generator=gen, device="cuda")
+    dy = torch.rand(shape + (channels[1],), generator=gen, device="cuda") + 0.5
+    for axis in range(dim):
+        # the last entry along the axis, in the middle of the others
+        at = [n // 2 for n in shape[1:]]
+        at[axis] = shape[1 + axis] - 1
+        spot = (0, *at, axis)
+        bad = x.clone()
+        x[spot], bad[spot] = 0.0, float("inf")
+        g0, _ = net.backward(x, dy, want_dx=False)
+        g1, _ = net.backward(bad, dy, want_dx=False)
+        w0, w1 = (cnn_ref.unflatten(g, dim, channels)[0] for g in (g0, g1))
+        assert np.array_equal(w0[1], w1[1])  # the bias gradient sees dy alone
+        for tap, d in enumerate(itertools.product((-1, 0, 1), repeat=dim)):
+            seen = all(0 <= a - b < n for a, b, n in zip(at, d, shape[1:]))
+            for ci in range(channels[0]):
+                row0, row1 = w0[0][tap, ci], w1[0][tap, ci]
+                if seen and ci == axis:
+                    assert not np.isfinite(row1).any(), (axis, tap, ci)
+                else:
+                    assert np.array_equal(row0, row1), (axis, tap, ci)
