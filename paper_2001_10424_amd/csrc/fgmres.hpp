@@ -47,13 +47,14 @@ inline int gm_blocks(int n) {
 }
 
 struct FgmState {
-  double R[kGmMaxRestart][kGmMaxRestart];       // R[j][i]: rotated column j, row i
+  // R[j][i]: row i of rotated column j; before that, of the first pass's
+  // coefficients
+  double R[kGmMaxRestart][kGmMaxRestart];
   double cs[kGmMaxRestart], sn[kGmMaxRestart];  // Givens rotations
-  double g[kGmMaxRestart];                      // rotated least-squares rhs
+  double g[kGmMaxRestart];                      // rotated least-squares rhs, then the
+                                                // solution y of the triangular system
   double gam[kGmMaxRestart + 1];                // its last entry after j steps
-  double h[2][kGmMaxRestart + 1];               // coefficients of the two passes
-  double sum[kGmMaxRestart + 1];                // summed partials (k_gm_sums)
-  double y[kGmMaxRestart];                      // solution of the triangular system
+  double h[kGmMaxRestart];                      // coefficients of the second pass
   double beta;                                  // ||r|| at the start of the cycle
   int it0;                                      // steps before this cycle
   int k;                                        // completed Arnoldi steps of the cycle
@@ -134,14 +135,14 @@ __device__ __forceinline__ void get_sums(const double* __restrict__ part, int nb
   __syncthreads();
 }
 
-// sums of more than kGmFold partials each, one block per sum: fs->sum takes
-// the place of the partials (one per sum)
-__global__ __launch_bounds__(kFinal) void k_gm_sums(const PcgState* cyc, FgmState* fs,
+// sums of more than kGmFold partials each, one block per sum: they take the
+// place of the partials (one per sum)
+__global__ __launch_bounds__(kFinal) void k_gm_sums(const PcgState* cyc, double* sums,
                                                     const double* part, int nb) {
   if (cyc->done) return;
   __shared__ double sh[kFinal / 64];
   const double v = sum_partials(part + (long)blockIdx.x * nb, nb, sh);
-  if (threadIdx.x == 0) fs->sum[blockIdx.x] = v;
+  if (threadIdx.x == 0) sums[blockIdx.x] = v;
 }
 
 // ------------------------------------------------------- Arnoldi steps
@@ -155,7 +156,7 @@ __device__ __forceinline__ void gm_step_end(PcgState* st, PcgState* cyc, FgmStat
                                             int j, bool last) {
   __shared__ double col[kGmMaxRestart], cs[kGmMaxRestart], sn[kGmMaxRestart];
   if (threadIdx.x <= j) {
-    col[threadIdx.x] = fs->h[0][threadIdx.x] + fs->h[1][threadIdx.x];
+    col[threadIdx.x] = fs->R[j][threadIdx.x] + fs->h[threadIdx.x];
     cs[threadIdx.x] = fs->cs[threadIdx.x];
     sn[threadIdx.x] = fs->sn[threadIdx.x];
   }
@@ -319,7 +320,8 @@ __global__ __launch_bounds__(kBlock) void k_gm_pass(int n, const PcgState* __res
   };
   if (i0 < n) fetch(i0);  // in flight beside the partials
   get_sums<Q>(part, nb, nv, hs);
-  if (blockIdx.x == 0 && threadIdx.x < nv) fs->h[PASS][threadIdx.x] = hs[threadIdx.x];
+  if (blockIdx.x == 0 && threadIdx.x < nv)
+    (PASS == 0 ? fs->R[nv - 1] : fs->h)[threadIdx.x] = hs[threadIdx.x];
   for (int i = i0; i < n; i += gridDim.x * kBlock) {
     if (i != i0) fetch(i);
     double x = double(wi);
@@ -374,7 +376,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_finish(PcgState* st, PcgState* cy
     if (lane == c) g = y;
     else if (lane < c) g -= Rc[lane] * y;
   }
-  if (lane < k) fs->y[lane] = g;
+  if (lane < k) fs->g[lane] = g;
 }
 
 // x += sum_{i<k} y_i z_i
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_update_x(int n, const PcgState* _
   for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
     double xi = double(x[i]);
 #pragma unroll 8
-    for (int l = 0; l < k; ++l) xi += fs->y[l] * double(Z[l * ldz + i]);
+    for (int l = 0; l < k; ++l) xi += fs->g[l] * double(Z[l * ldz + i]);
     x[i] = T(xi);
   }
 }

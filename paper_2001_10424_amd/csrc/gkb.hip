@@ -595,6 +595,19 @@ const Op<double>& op_of<double>(gkb_ctx* c) { return c->op64; }
 template <>
 const Op<float>& op_of<float>(gkb_ctx* c) { return c->op32; }
 
+// the product of the folded PCG iterations: with CG on a finest level of box
+// legs, while every block of the next kernel can sum the partials itself (in
+// 2D up to about 1024^2 cells); tile 0: not folded
+template <typename T>
+LegPlan folded_product(const gkb_ctx* c, const Inner<T>& in) {
+  const Level<T>& L0 = in.lv[0];
+  if (c->opt.inner == GKB_INNER_JACOBI || c->opt.krylov != GKB_KRYLOV_CG || !L0.leg.tile ||
+      marches(L0.leg))
+    return LegPlan();
+  const LegPlan p = apply_plan(L0.g);
+  return std::max(p.nblocks, L0.leg.nblocks) <= kFoldParts ? p : LegPlan();
+}
+
 template <typename T>
 int pcg_iterations(gkb_ctx* c, Inner<T>& in, int count) {
   const Level<T>& L0 = in.lv[0];
@@ -612,8 +625,8 @@ int pcg_iterations(gkb_ctx* c, Inner<T>& in, int count) {
   // launches: the direction update joins the product (alternating as above)
   // and the three scalar steps join the kernels that need them, 4 + legs
   // kernels instead of 7 + legs (common.hpp).
-  const LegPlan ap = L0.leg.tile && !marches(L0.leg) ? apply_plan(L0.g) : LegPlan();
-  if (!jac && ap.tile && std::max(ap.nblocks, L0.leg.nblocks) <= kFoldParts && in.p2) {
+  const LegPlan ap = folded_product(c, in);
+  if (ap.tile) {
     const int xb = fold_blocks(n);
     for (int it = 0; it < count; ++it) {
       T* pold = (it % 2 == 0) ? in.p : in.p2;
@@ -687,6 +700,12 @@ int ensure_graph(gkb_ctx* c, Inner<T>& in, int count) {
 // x += Z y, and the next cycle's start from the true residual r = f - M x
 // (f in in.rprev).  Every kernel skips once its flag is set, so the launch
 // sequence is fixed and is captured as one graph.
+// where the sums of more than kGmFold partials go: behind the partials
+template <typename T>
+double* gm_sums(const gkb_ctx* c, const Inner<T>& in) {
+  return in.gm_part + (size_t)(c->opt.fgmres_restart + 1) * gm_blocks(in.lv[0].g.m_full);
+}
+
 template <typename T, int Q>
 void fgmres_orthogonalise(gkb_ctx* c, Inner<T>& in, int nv, const T* z, T* w) {
   const int n = in.lv[0].g.m_full, gb = gm_blocks(n);
@@ -697,8 +716,9 @@ void fgmres_orthogonalise(gkb_ctx* c, Inner<T>& in, int nv, const T* z, T* w) {
   // partials of nv sums as the next kernel takes them
   auto ready = [&](double* p, int count) -> double* {
     if (fold) return p;
-    k_gm_sums<<<count, kFinal, 0, s>>>(in.gm_cyc, in.gm_fs, p, gb);
-    return in.gm_fs->sum;
+    double* const sums = gm_sums(c, in);
+    k_gm_sums<<<count, kFinal, 0, s>>>(in.gm_cyc, sums, p, gb);
+    return sums;
   };
   const int nb = fold ? gb : 1;
   if (z)
@@ -724,7 +744,7 @@ void fgmres_cycle(gkb_ctx* c, Inner<T>& in) {
   hipStream_t s = c->cs;
   const bool jac = c->opt.inner == GKB_INNER_JACOBI;
   const bool learned = c->opt.inner == GKB_INNER_LEARNED && learned_has_net(c->learned);
-  const double* pww = gm_folded(n) ? in.gm_part : in.gm_fs->sum;  // partials of w.w
+  const double* pww = gm_folded(n) ? in.gm_part : gm_sums(c, in);  // partials of w.w
   const bool at = jac && c->csr && L0.op.eta != T(0);
   for (int j = 0; j < R; ++j) {
     T* vj = in.gm_V + j * ld;
@@ -1395,8 +1415,10 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
       CK(c->mem.arr(&lv.b, m));
       CK(c->mem.arr(&lv.x, m));
     }
-    CK(c->mem.arr(&lv.t, m));
-    CK(c->mem.arr(&lv.rb, m));
+    if (c->opt.inner != GKB_INNER_JACOBI) {  // iterates and residual of the V-cycle
+      CK(c->mem.arr(&lv.t, m));
+      CK(c->mem.arr(&lv.rb, m));
+    }
     if (l >= 1 && l < L - 1) {
       CK(c->mem.arr(&lv.dinv, m));
       face_op<T, kDiag>(c, lv.op, lv.fl, nullptr, nullptr, lv.dinv, T(0), nullptr, nullptr);
@@ -1416,7 +1438,8 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
   CK(c->mem.arr(&in.r, m));
   CK(c->mem.arr(&in.z, m));
   CK(c->mem.arr(&in.p, m));
-  if (((sizeof(T) == 4 && c->fl0.tiled) || (in.lv[0].leg.tile && !marches(in.lv[0].leg))) && c->opt.inner != GKB_INNER_JACOBI)
+  if ((sizeof(T) == 4 && c->fl0.tiled && c->opt.inner != GKB_INNER_JACOBI) ||
+      folded_product(c, in).tile)
     CK(c->mem.arr(&in.p2, m));
   CK(c->mem.arr(&in.q, m));
   CK(c->mem.arr(&in.rprev, m));
@@ -1427,7 +1450,8 @@ int build_inner(gkb_ctx* c, Inner<T>& in, const std::vector<Coef<T>>& coef) {
     CK(c->mem.arr(&in.gm_Z, (size_t)R * m));
     CK(c->mem.arr(&in.gm_fs, 1));
     CK(c->mem.arr(&in.gm_cyc, 1));
-    CK(c->mem.arr(&in.gm_part, (size_t)(R + 1) * gm_blocks(m) * (gm_folded(m) ? 2 : 1)));
+    // two sets of partials, or one and its sums (gm_sums)
+    CK(c->mem.arr(&in.gm_part, (size_t)(R + 1) * (gm_folded(m) ? 2 * gm_blocks(m) : gm_blocks(m) + 1)));
   }
   // Jacobi preconditioner 1/diag(M) (0 at non-unknown faces)
   CK(c->mem.arr(&in.dinv, m));
@@ -1581,9 +1605,8 @@ int setup_impl(gkb_ctx* c, const gkb_grid* grid, const double* visc, double eta,
     const Grid& g = c->grids[l];
     Op<double> op = make_op<double>(g, eta, c->coef64[l], c->varmu);
     FaceLaunch fl = face_launch(g, 4, c->opt.stencil);
-    double *xa, *ya;
-    CK(c->mem.arr(&xa, g.m_full));
-    CK(c->mem.arr(&ya, g.m_full));
+    double *xa = c->u, *ya = c->v;  // not in use yet; zeros again below
+    k_fill<double><<<vec_blocks(m), kBlock, 0, c->cs>>>(m, 0.0, ya);
     std::vector<double> x0(g.m_full);
     unsigned s = 12345u;
     for (auto& v : x0) {
@@ -1604,6 +1627,7 @@ int setup_impl(gkb_ctx* c, const gkb_grid* grid, const double* visc, double eta,
     }
     c->omega[l] = 1.6 / (1.05 * lam);
   }
+  for (double* v : {c->u, c->v}) k_fill<double><<<vec_blocks(m), kBlock, 0, c->cs>>>(m, 0.0, v);
   if (opt->smoother == GKB_SMOOTH_HYBRID && opt->inner != GKB_INNER_JACOBI) CK(edge_setup(c));
   // coarsest level: dense FP64 inverse of M on the unknown faces
   if (opt->inner != GKB_INNER_JACOBI) {
