@@ -122,3 +122,31 @@ def test_precondition_on_its_input(name, smoother, precision):
         assert gk.library().gkb_precondition(s._ctx, prec, p, p) == 0
         assert torch.equal(r, z)
         s.close()
+
+
+@pytest.mark.parametrize("smoother,precision", [("jacobi", "fp64"), ("hybrid", "mixed")])
+def test_large_2d_legs_with_separate_scalar_steps(smoother, precision):
+    """2D grids with more partials than the folded PCG steps sum (2048): legs
+    beside the separate update and scalar kernels, against the generic
+    kernels (stencil = 1), in the tolerances of the smaller grids."""
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] large 2D legs", smoother, precision, flush=True)
+    g = P.Grid(2, (1344, 1088, 1), 1 / 1088, (D, N, D, D, D, D), -1)
+    nu = 1 if smoother == "hybrid" else 2
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    r = _dev(np.random.default_rng(11).standard_normal(g.m_full), dt)
+    f = _dev(P.random_vector(g, 6), torch.float64)
+    out = []
+    for stencil in (0, 1):
+        s = gk.Solver(g, None, 10.0, inner="mg", stencil=stencil, smoother=smoother, nu_pre=nu,
+                      nu_post=nu, precision=precision)
+        x, it = s.inner_solve(f, 1e-4)
+        res = f - s.apply("M", x)
+        assert float(res.norm() / f.norm()) <= (1.0001e-4 if precision == "fp64" else 1e-2)
+        out.append((s.precondition(r, precision).double(), it))
+        s.close()
+    (a, ia), (b, ib) = out
+    eps = 2.0 ** -52 if precision == "fp64" else 2.0 ** -23
+    assert float((a - b).norm()) <= 1e3 * eps * float(b.norm())
+    assert abs(ia - ib) <= 1 + 0.02 * ib, (ia, ib)

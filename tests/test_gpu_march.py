@@ -75,3 +75,37 @@ def test_slabs_too_thin_to_march(n, eta):
         assert np.abs(a.cpu().numpy() - b).max() <= 64 * 2.0 ** -52 * np.abs(b).max()
     with pytest.raises(RuntimeError, match="invalid argument"):
         gk.Solver(g, None, eta, inner="mg")
+
+
+@pytest.mark.parametrize("transfer,precision", [
+    ("smooth", "fp64"), ("smooth", "mixed"), ("div", "fp64")])
+@pytest.mark.parametrize("name", ["ragged", "thin", "nat", "nat_x"])
+def test_marching_legs_in_pcg(name, transfer, precision):
+    """Inner solves whose r.z comes from the marching legs' partial sums: the
+    same iterates as with the separate kernels.  A face missed or counted twice
+    changes r.z by 1e-6 of it, a row of faces by 1e-4.
+
+    Tolerance: rounding of up to 40 operators a cycle adds up like a random
+    walk, sqrt(40) times 3 eps, and the recurrences carry it along (a factor of
+    5): 1e2 eps per iteration.  That holds for the first iterations and without
+    a pinned cell, whose single mode CG finds first and then again from
+    rounding."""
+    import dataclasses
+
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] march in PCG", name, transfer, precision, flush=True)
+    g = dataclasses.replace(GRIDS[name], pin=-1)
+    f = torch.tensor(P.random_vector(g, 6), dtype=torch.float64, device="cuda")
+    out = []
+    for stencil in (0, 1):
+        s = gk.Solver(g, None, 1e2, inner="mg", stencil=stencil, nu_pre=2, nu_post=2,
+                      mg_transfer=transfer, precision=precision)
+        out.append(s.inner_solve(f, 0.3))
+        s.close()
+    (x, its), (xs, its_s) = out
+    eps = 2.0 ** -52 if precision == "fp64" else 2.0 ** -23
+    err = float((x - xs).norm() / xs.norm())
+    print("   iterations", its, its_s, "relative difference", err, flush=True)
+    assert its == its_s and its >= 8
+    assert err <= 1e2 * eps * its
