@@ -147,7 +147,9 @@ typedef struct {
   int max_sweeps;       /* cap on defect-correction sweeps */
   int check_every;      /* inner iterations between host convergence checks */
   int use_graphs;       /* capture inner iterations in HIP graphs (1) or not */
-  int stencil;          /* 0: LDS-tiled 3D stencil kernel where it applies (3D
+  int stencil;          /* 0: fused V-cycle legs on the levels that gain from
+                           them (V(2,2) Jacobi, V(1,1) hybrid), else the
+                           LDS-tiled 3D stencil kernel where it applies (3D
                            grids whose +x, +y, +z sides are DIRICHLET), generic
                            face kernel elsewhere; 1: generic face kernel only */
   int smoother;         /* GKB_SMOOTH_JACOBI or GKB_SMOOTH_HYBRID */
@@ -319,7 +321,7 @@ int gkb_apply(gkb_ctx *c, int op, int precision, const void *x, void *y);
 
 /* One preconditioner application z = B r on the finest grid (B = one
    V-cycle, or diag(M)^-1 for the Jacobi inner solver), FP64 or FP32 as
-   gkb_apply.  Device pointers. */
+   gkb_apply.  Device pointers; z may be r. */
 int gkb_precondition(gkb_ctx *c, int precision, const void *r, void *z);
 
 /* Inner solve M x = f with the context's inner solver (x0 = 0), FP64 device
@@ -331,7 +333,8 @@ int gkb_inner_solve(gkb_ctx *c, const double *f, double *x, double tol,
 
 /* FP64 saddle residual res_w = g - W w - A p, res_r = r - A^T w (device);
    norms (host, 4 doubles): ||[res_w; res_r]||, ||res_w||, ||res_r||,
-   ||[g; r]||.  res_w / res_r may be NULL when only the norms are wanted. */
+   ||[g; r]||.  res_w / res_r may be NULL when only the norms are wanted; res_w
+   may be g, and res_r may lie on r, p or g. */
 int gkb_residual(gkb_ctx *c, const double *g, const double *r, const double *w,
                  const double *p, double *res_w, double *res_r, double *norms);
 
@@ -368,7 +371,8 @@ int gkb_time_kernel(gkb_ctx *c, int kernel, int reps, double *avg_ms);
    hipMalloc): the FP64 saddle residual of gkb_residual for viscosity mu = 1,
    without a solver context.  grid as for gkb_setup; g, w (faces) and r, p
    (cells) are caller-owned device FP64 arrays; res_r (cells, required) and
-   res_w (faces, may be NULL) receive the residual blocks; norms (host, 4
+   res_w (faces, may be NULL) receive the residual blocks, where they may lie on
+   inputs as in gkb_residual; norms (host, 4
    doubles) as gkb_residual.  Work is queued on hip_stream (NULL = the null
    stream) and complete on return.  Allocates nothing: its reduction partials
    live in a fixed device array of 2 MiB (one per GPU, kept until the process

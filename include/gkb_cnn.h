@@ -15,7 +15,7 @@
  * Input channels: the components of rt on the faces below / left of each
  * cell (u, v[, w]) divided by s, then log(mu) of the cell; output channels:
  * the correction of the same faces.  Arithmetic: BF16 weights and
- * activations on MFMA (v_mfma_f32_16x16x16_bf16) with FP32 accumulation;
+ * activations on MFMA (v_mfma_f32_16x16x32_bf16) with FP32 accumulation;
  * FP32 master weights and Adam state.
  *
  * Parameter layout (flat FP32, per layer l): W_l[tap][c_in][c_out] then
@@ -55,12 +55,13 @@ int gkb_cnn_set_params(gkb_cnn *n, const float *host_params);
 int gkb_cnn_get_params(const gkb_cnn *n, float *host_params);
 
 /* y = C_theta(x) for a batch of `batch` grids of nx * ny * nz points (nz = 1
-   in 2D); x [batch][points][c_0], y [batch][points][c_L], FP32. */
+   in 2D); x [batch][points][c_0], y [batch][points][c_L], FP32.  y may lie on
+   x. */
 int gkb_cnn_forward(gkb_cnn *n, int nx, int ny, int nz, int batch, const float *x, float *y);
 
 /* Gradient of sum(dy .* C_theta(x)) with respect to the parameters (grad,
-   HOST, param_count floats) and to x (dx, device, may be NULL); recomputes
-   the forward pass. */
+   HOST, param_count floats) and to x (dx, device, may be NULL, may lie on dy
+   or x); recomputes the forward pass. */
 int gkb_cnn_backward(gkb_cnn *n, int nx, int ny, int nz, int batch, const float *x,
                      const float *dy, float *dx, float *grad_host);
 

@@ -22,7 +22,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 
-// tile of output points: rows of 32 points, 16 rows
+// tile of output points: rows of 32 points, 16 rows, whatever the grid (a grid
+// two points wide is still no slower than single points gathered from memory,
+// one point wide it is: 65536 x 1, 3 -> 8 -> 8 -> 2 channels 54 against 39 us)
 template <int DIM>
 struct CTile {
   static constexpr int TX = 32, TY = DIM == 3 ? 4 : 16, TZ = DIM == 3 ? 4 : 1;
@@ -457,7 +459,7 @@ __device__ __forceinline__ s16x4 lds_transposed(const uint16_t* a) {
 // block's sums hold a NaN it forms them again without those points (their rows
 // left out, zeros read in a row).  Leaving them out at once, by a mask or by the
 // address, cost 3 to 4 us a layer at 62^3 x 2 points.
-// 64^3 x 2 points: 14 us for 8 x 8 channels and 12 us for 4 x 8; 235 and 142
+// 64^3 x 2 points: 15 us for 8 x 8 channels and 14 us for 4 x 8; 235 and 142
 // us with single BF16 values gathered from memory.
 template <int DIM, int CG>
 constexpr int wgrad_tiles() { return (CTile<DIM>::TAPS * CG + 15) / 16; }
@@ -689,7 +691,7 @@ void conv_layer(hipStream_t s, int dim, const CnnGeom& g, const ConvIn& in, cons
   }
 }
 
-// blocks of the weight gradient: two per CU (12-15 us a layer at 64^3 x 2; one
+// blocks of the weight gradient: two per CU (14-15 us a layer at 64^3 x 2; one
 // per CU takes 16-18 us and saves nothing in the reduction, 4.7 us)
 int wgrad_blocks(int dim, const CnnGeom& g) {
   const long tiles = dim == 2 ? tile_count<2>(g) : tile_count<3>(g);

@@ -20,7 +20,6 @@ __host__ __device__ inline uint16_t f2bf(float f) {
   u += 0x7FFFu + ((u >> 16) & 1u);  // round to nearest even
   return uint16_t(u >> 16);
 }
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
 constexpr int kMaxLayers = 8;
 

@@ -713,14 +713,27 @@ LegPlan plan_march(const Grid& g, int id) {
 // box legs take these).  One V(2,2) cycle in us, separate kernels / march on
 // all levels above 40^3 cells:
 //                   SMOOTH FP64  SMOOTH FP32   DIV FP64   DIV FP32
-//   64 x 64 x 64      142 / 131    130 / 124   119 / 123  107 / 116
-//   80 x 64 x 72      177 / 150    156 / 134   162 / 139  132 / 125
-//   96 x 80 x 112     237 / 214    198 / 175   214 / 197  169 / 158
-//   128 x 128 x 128   362 / 319    279 / 232   278 / 284  195 / 218
-//   144 x 112 x 96    333 / 274    265 / 223   271 / 247  199 / 208
+//   64 x 64 x 64      133 / 131    119 / 124   119 / 123  107 / 116
+//   80 x 64 x 72      177 / 150    156 / 134   163 / 138  132 / 125
+//   96 x 80 x 112     237 / 214    198 / 175   215 / 192  169 / 158
+//   128 x 128 x 128   346 / 318    251 / 235   278 / 284  195 / 218
+//   144 x 112 x 96    333 / 274    265 / 223   270 / 248  199 / 208
+//   192 x 192 x 96    556 / 507    351 / 322
+//   160 x 160 x 32    216 / 219    173 / 167   205 / 199
+//   32 x 160 x 160    239 / 208    183 / 171   232 / 187
+//   128 x 16 x 128    134 / 130    117 / 124
+//   16 x 128 x 128    167 / 131    147 / 129
+//   248 x 32 x 32     141 / 129    127 / 123   123 / 121
+//   240 x 64 x 64     218 / 224    182 / 171   190 / 204
+//   120 x 64 x 64     160 / 167    142 / 141   149 / 151
+//   160 x 160 x 160                            543 / 454
+//   240 x 128 x 128                            473 / 448
 // With the SMOOTH transfers, whose interpolation the tiled stencil does not
-// take along, always; with DIV in FP64 where the 64 cells wide tiles of the
-// separate kernels leave lanes idle (in FP32 the sign changes with the size).
+// take along, always: 0.95 to 1.28 times as fast, the more the larger the grid.
+// With DIV in FP64 where the width is no multiple of the 64 cells wide tiles of
+// the separate kernels, whose last one then leaves lanes idle; with few of them
+// idle (120, 240, 248) the two are even on average.  In FP32 the sign
+// changes with the size.
 LegPlan march_plan(const Grid& g, int elem, bool smooth) {
   // 32-bit byte offsets
   if (g.dim != 3 || (long)g.m_full * elem >= (1L << 31)) return LegPlan();
