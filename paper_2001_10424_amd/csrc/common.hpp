@@ -192,7 +192,8 @@ __device__ __forceinline__ double fold_beta(PcgState* st, double rz_new, bool le
   }
   return b;
 }
-__device__ __forceinline__ double fold_alpha(PcgState* st, double pq, bool lead) {
+// false: breakdown, the iterate stays as it is and the solve ends
+__device__ __forceinline__ bool fold_alpha(PcgState* st, double pq, bool lead, double& alpha) {
   const double rz = st->rz, a = rz / pq;
   if (lead) {
     pcg_set_alpha(st, pq);
@@ -200,7 +201,8 @@ __device__ __forceinline__ double fold_alpha(PcgState* st, double pq, bool lead)
     st->it_x = st->it;
     st->fresh = 0;
   }
-  return (!(pq > 0.0) || !isfinite(a)) ? 0.0 : a;
+  alpha = a;
+  return pq > 0.0 && isfinite(a);
 }
 // true: the iteration ends here
 __device__ __forceinline__ bool fold_check(PcgState* st, double rr, bool lead) {

@@ -596,7 +596,9 @@ __global__ __launch_bounds__(kBlock) void k_pcg_xr_fold(int n, PcgState* st,
   T xi = x[e], pi = p[e], ri = r[e], qi = q[e];
   double pq;
   if (!fold_sum_if<kBlock>(done, fold_share<kBlock>(part_pq, npq), fold, pq)) return;
-  const T a = T(fold_alpha(st, pq, blockIdx.x == 0 && threadIdx.x == 0));
+  double alpha;
+  if (!fold_alpha(st, pq, blockIdx.x == 0 && threadIdx.x == 0, alpha)) return;
+  const T a = T(alpha);
   double s = 0.0;
   while (i < n) {
     x[i] = xi + a * pi;

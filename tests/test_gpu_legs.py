@@ -150,3 +150,31 @@ def test_large_2d_legs_with_separate_scalar_steps(smoother, precision):
     eps = 2.0 ** -52 if precision == "fp64" else 2.0 ** -23
     assert float((a - b).norm()) <= 1e3 * eps * float(b.norm())
     assert abs(ia - ib) <= 1 + 0.02 * ib, (ia, ib)
+
+
+@pytest.mark.parametrize("name,smoother,precision", [
+    ("2d_small", "hybrid", "fp64"), ("3d_medium", "jacobi", "fp64"), ("3d_small", "jacobi", "mixed")])
+def test_breakdown_keeps_the_iterate(name, smoother, precision):
+    """A right-hand side that is not finite ends an inner solve in its first
+    update: the error code, and the iterate of that time (0), also where the
+    update is folded."""
+    import ctypes as C
+
+    import torch
+    import paper_2001_10424_amd as gk
+    from paper_2001_10424_amd import _abi
+    print("[case] breakdown", name, smoother, precision, flush=True)
+    g = GRIDS[name]
+    nu = 1 if smoother == "hybrid" else 2
+    for stencil in (0, 1):
+        s = gk.Solver(g, None, 10.0, inner="mg", stencil=stencil, smoother=smoother, nu_pre=nu,
+                      nu_post=nu, precision=precision)
+        for bad in (float("nan"), float("inf")):
+            f = _dev(P.random_vector(g, 6), torch.float64)
+            f[int(torch.nonzero(f)[f.count_nonzero() // 2])] = bad
+            x, it = torch.ones_like(f), C.c_int(-1)
+            rc = gk.library().gkb_inner_solve(s._ctx, C.c_void_p(f.data_ptr()),
+                                              C.c_void_p(x.data_ptr()), 1e-4, C.byref(it))
+            assert (rc, it.value) == (_abi.GKB_ENAN, 0)
+            assert float(x.abs().max()) == 0.0
+        s.close()

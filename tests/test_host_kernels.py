@@ -83,20 +83,24 @@ void run_block(int block, int blocks, std::function<void()> kernel, std::functio
 
 def test_update_of_a_block_that_starts_while_the_solve_ends(tmp_path):
     """The folded PCG update meets p.q <= 0: block 0 ends the solve, and a
-    block whose waves read the flag before and after that leaves x and r as
-    they are (alpha = 0)."""
+    block leaves x and r as they are, whether its waves read the flag before
+    and after that or all before, also where the direction is not finite."""
     _run(tmp_path, BLOCK + r"""
 int main() {
   const int n = 512;
   std::vector<double> x(n, 3.0), r(n, 5.0), p(n, 1.0), q(n, 1.0), part(256), rr(2, -1.0);
   for (int i = 0; i < 256; ++i) part[i] = i < 128 ? 1.0 : -2.0;  // the sum is negative
+  p[300] = q[310] = NAN;
   PcgState st{};
   st.rz = 1.0;
-  run_block(1, 2, [&] { k_pcg_xr_fold<double>(n, &st, part.data(), 256, p.data(), q.data(), x.data(),
-                                              r.data(), rr.data()); },
-            [&] { st.done = 1; });
-  for (int i = 0; i < n; ++i)
-    if (x[i] != 3.0 || r[i] != 5.0) return std::printf("entry %d: %g %g\n", i, x[i], r[i]), 1;
+  for (int flag : {1, 0}) {
+    st.done = 0;
+    run_block(1, 2, [&] { k_pcg_xr_fold<double>(n, &st, part.data(), 256, p.data(), q.data(),
+                                                x.data(), r.data(), rr.data()); },
+              [&] { st.done = flag; });
+    for (int i = 0; i < n; ++i)
+      if (x[i] != 3.0 || r[i] != 5.0) return std::printf("entry %d: %g %g\n", i, x[i], r[i]), 1;
+  }
   return 0;
 }
 """)
