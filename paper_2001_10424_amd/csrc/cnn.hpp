@@ -156,8 +156,10 @@ struct gkb_cnn {
   uint16_t *wf = nullptr, *wd = nullptr;  // [L][taps][256]
   float* bias = nullptr;                  // [L][16]
   int adam_t = 0;
-  // workspace (grown on demand)
+  // workspace (grown on demand; a graph that holds its buffers is valid while
+  // buffers is what it was at the capture)
   long cap = 0;
+  long buffers = 0;
   uint16_t* act[gkb::kMaxLayers] = {nullptr};  // layer inputs, [P][chan_group]
   uint16_t *dz0 = nullptr, *dz1 = nullptr;
   float* y = nullptr;      // output [P][c_L]
@@ -211,6 +213,7 @@ int cnn_reserve(gkb_cnn* n, long P) {
   if (P <= 0 || P > 0x7fffffffL) return GKB_EINVAL;
   if (P <= n->cap) return GKB_OK;
   n->cap = 0;
+  n->buffers += 1;
   auto grow = [&](auto*& p, size_t bytes) {
     if (p) (void)hipFree(p);
     p = nullptr;

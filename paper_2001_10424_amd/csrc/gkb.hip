@@ -190,6 +190,7 @@ struct Inner {
   int graph_mode = -1;
   hipGraphExec_t graph_fcg = nullptr;
   int graph_fcg_len = 0;
+  long graph_fcg_net = -1;  // the network's buffers at the capture
   // inner FGMRES: basis V (restart + 1 vectors) and preconditioned vectors Z
   // (restart), FP64 Hessenberg state, the cycle flag and the dot partials;
   // one restart cycle is one captured graph
@@ -198,7 +199,7 @@ struct Inner {
   PcgState* gm_cyc = nullptr;
   double* gm_part = nullptr;
   hipGraphExec_t graph_gm = nullptr;
-  bool graph_gm_learned = false;  // the captured cycle applies the network
+  long graph_gm_net = -1;  // the network's buffers if the cycle applies it, else -1
 };
 
 // the learned preconditioner z = V(r) + theta c applied to r_in
@@ -782,7 +783,8 @@ int fgmres_solve(gkb_ctx* c, const double* f, double* x_out, double tol, int* it
   // before the cycle is captured or replayed
   const bool learned = c->opt.inner == GKB_INNER_LEARNED && learned_has_net(c->learned);
   if (learned) CK(learned_prepare(c));
-  if (in.graph_gm && in.graph_gm_learned != learned) {
+  const long net = learned ? learned_buffers(c->learned) : -1;
+  if (in.graph_gm && in.graph_gm_net != net) {
     (void)hipGraphExecDestroy(in.graph_gm);
     in.graph_gm = nullptr;
   }
@@ -798,7 +800,7 @@ int fgmres_solve(gkb_ctx* c, const double* f, double* x_out, double tol, int* it
     const hipError_t ie = hipGraphInstantiate(&in.graph_gm, gr, nullptr, nullptr, 0);
     (void)hipGraphDestroy(gr);
     HIPCK(ie);
-    in.graph_gm_learned = learned;
+    in.graph_gm_net = net;
   }
   PcgState hs;
   // every cycle takes at least one Arnoldi step, so inner_maxit bounds the

@@ -13,6 +13,7 @@ namespace {
 constexpr int kLearnedDeclined = 2;
 bool learned_enabled(Learned* L);
 bool learned_has_net(Learned* L);
+long learned_buffers(Learned* L);  // changes when the network's workspace moves
 bool learned_capturing(Learned* L);
 void learned_reset(Learned* L);
 template <typename T>

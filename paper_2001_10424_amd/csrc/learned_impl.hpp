@@ -263,6 +263,7 @@ namespace {
 
 bool learned_enabled(Learned* L) { return L && L->net && !L->off; }
 bool learned_has_net(Learned* L) { return L && L->net; }
+long learned_buffers(Learned* L) { return L->net->buffers; }
 void learned_reset(Learned* L) {
   if (L) {
     L->off = false;
@@ -439,7 +440,7 @@ int learned_solve(gkb_ctx* c, const double* f, double* x_out, double tol, int* i
   }
   const int chunk = std::max(1, c->opt.check_every);
   if (c->opt.use_graphs) {
-    if (!(in.graph_fcg && in.graph_fcg_len == chunk)) {
+    if (!(in.graph_fcg && in.graph_fcg_len == chunk && in.graph_fcg_net == net->buffers)) {
       if (in.graph_fcg) (void)hipGraphExecDestroy(in.graph_fcg);
       in.graph_fcg = nullptr;
       hipGraph_t gr;
@@ -449,6 +450,7 @@ int learned_solve(gkb_ctx* c, const double* f, double* x_out, double tol, int* i
       HIPCK(hipGraphInstantiate(&in.graph_fcg, gr, nullptr, nullptr, 0));
       (void)hipGraphDestroy(gr);
       in.graph_fcg_len = chunk;
+      in.graph_fcg_net = net->buffers;
     }
   }
   for (;;) {

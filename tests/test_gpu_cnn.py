@@ -534,3 +534,29 @@ def test_variable_viscosity_2d_learned_pipeline():
           f"{res['mg']['inner_iterations']} learned {res['learned']['inner_iterations']} "
           f"gain {res['learned']['learned_gain']:.3g} fallbacks {res['learned']['fallbacks']}",
           flush=True)
+
+
+@pytest.mark.parametrize("krylov", ["cg", "fgmres"])
+def test_network_workspace_grows_between_solves(krylov):
+    """A larger batch moves the network's workspace, which the captured inner
+    iterations of a context hold: the next solve captures them anew and gives
+    the same bits."""
+    _say("learned workspace", krylov)
+    import torch
+    gk = _gk()
+    pr = _small_problem(9, n=16)
+    net = gk.CNN(3, (4, 8, 8, 3), seed=0)
+    s = _solver(gk, pr, inner="learned", krylov=krylov, learned_min_gain=-1.0, smoother="hybrid",
+                nu_pre=1, nu_post=1, inner_maxit=20000)
+    s.attach_cnn(net)
+    out, keep = [], []
+    for batch in (0, 4, 40):
+        if batch:
+            net.forward(torch.randn((batch, 16, 16, 16, 4), device="cuda"))
+            keep.append(torch.full((64 << 20,), float("nan"), device="cuda"))  # where buffers were
+        out.append(s.solve(_dev(pr.g), _dev(pr.r), tol=1e-4))
+        assert out[-1][2]["learned_solves"] > 0
+    for w, p, info in out[1:]:
+        assert torch.equal(w, out[0][0]) and torch.equal(p, out[0][1])
+        assert info["inner_iterations"] == out[0][2]["inner_iterations"]
+    s.close()
