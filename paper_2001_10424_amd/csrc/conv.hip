@@ -241,7 +241,8 @@ __global__ __launch_bounds__(kThreads) void k_conv(CnnGeom g, const void* __rest
                                                    void* __restrict__ out, int cout,
                                                    const uint16_t* __restrict__ mask,
                                                    const int* __restrict__ skip1,
-                                                   const int* __restrict__ skip2) {
+                                                   const int* __restrict__ skip2,
+                                                   unsigned first) {
   typedef CTile<DIM> C;
   if ((skip1 && *skip1) || (skip2 && *skip2)) return;
   constexpr int TPM = 32 / CG;                       // taps per MFMA
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(kThreads) void k_conv(CnnGeom g, const void* __rest
   __shared__ __align__(16) uint16_t sh[C::N * CG];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int m = lane & 15, kg = lane >> 4;
-  const TileAt t = tile_at<DIM>(g, blockIdx.x);
+  const TileAt t = tile_at<DIM>(g, first + blockIdx.x);
   // the lane's eight K values of MFMA j: CG >= 8: tap t0, channels c0 ..;
   // CG = 4: taps t0 and t0 + 1
   s16x8 wr[NM];
@@ -601,26 +602,34 @@ __global__ __launch_bounds__(kThreads) void k_wgrad_reduce(WgradSum ws, int taps
 }
 
 constexpr unsigned kPairBlocks = 1024;  // four per CU, which fit
+constexpr unsigned kMaxBlocks = 1u << 23;  // a launch has less than 2^32 threads
 
 template <int DIM, int CG, bool F32>
 void launch_conv(hipStream_t s, const CnnGeom& g, const ConvIn& in, const uint16_t* w,
                  const float* bias, ConvOut mode, void* out, int cout, const uint16_t* mask,
                  const int* skip1, const int* skip2) {
-  const unsigned blocks = unsigned(tile_count<DIM>(g));
-  const bool pair = cout <= 8;
-  const unsigned grid = pair ? std::min((blocks + 7) / 8 * 8, kPairBlocks) : blocks;
-  auto go = [&](auto kernel) {
+  const unsigned tiles = unsigned(tile_count<DIM>(g));
+  auto several = [&](auto kernel) {  // tiles per block
+    const unsigned grid = std::min((tiles + 7) / 8 * 8, kPairBlocks);
     kernel<<<grid, kThreads, 0, s>>>(g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2);
   };
+  auto one = [&](auto kernel) {
+    for (unsigned first = 0; first < tiles; first += kMaxBlocks)
+      kernel<<<std::min(tiles - first, kMaxBlocks), kThreads, 0, s>>>(
+          g, in.p, in.c, w, bias, out, cout, mask, skip1, skip2, first);
+  };
+  const bool pair = cout <= 8;
   switch (mode) {
     case kOutReluBf16:
-      pair ? go(k_conv_pair<DIM, CG, F32, kOutReluBf16>) : go(k_conv<DIM, CG, F32, kOutReluBf16>);
+      pair ? several(k_conv_pair<DIM, CG, F32, kOutReluBf16>)
+           : one(k_conv<DIM, CG, F32, kOutReluBf16>);
       break;
     case kOutF32:
-      pair ? go(k_conv_pair<DIM, CG, F32, kOutF32>) : go(k_conv<DIM, CG, F32, kOutF32>);
+      pair ? several(k_conv_pair<DIM, CG, F32, kOutF32>) : one(k_conv<DIM, CG, F32, kOutF32>);
       break;
     case kOutMaskBf16:
-      pair ? go(k_conv_pair<DIM, CG, F32, kOutMaskBf16>) : go(k_conv<DIM, CG, F32, kOutMaskBf16>);
+      pair ? several(k_conv_pair<DIM, CG, F32, kOutMaskBf16>)
+           : one(k_conv<DIM, CG, F32, kOutMaskBf16>);
       break;
   }
 }

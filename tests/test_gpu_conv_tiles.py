@@ -178,3 +178,21 @@ def test_non_finite_weight_gradients_stay_local(dim, shape, channels):
                     assert not np.isfinite(row1).any(), (axis, tap, ci)
                 else:
                     assert np.array_equal(row0, row1), (axis, tap, ci)
+
+
+def test_more_tiles_than_a_launch_takes():
+    """A batch of more small grids than one launch has blocks for (2^32
+    threads): every part of it the same bits as by itself."""
+    import torch
+    import paper_2001_10424_amd as gk
+    print("[case] conv batch", flush=True)
+    n, m = (1 << 24) + 11, 4096
+    net = gk.CNN(2, (1, 12), seed=3)
+    part = torch.randn((m, 1, 1, 1), generator=torch.Generator(device="cuda").manual_seed(5),
+                       device="cuda")
+    want = net.forward(part)
+    x = part.repeat(n // m + 1, 1, 1, 1)[:n].contiguous()
+    y = net.forward(x)
+    full = n // m * m
+    assert bool((y[:full].view(-1, m, 12) == want.view(1, m, 12)).all())
+    assert torch.equal(y[full:], want[:n - full])
